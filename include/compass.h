@@ -117,7 +117,12 @@ typedef struct {
  * buffer takes at most 8.5 GiB of scratch (environment: COMPASS_TWO_PHASE_
  * BYTES sets that budget, COMPASS_SURVIVOR_CAP_ROWS caps the buffer's rows;
  * both exist to force many batches in tests).  E_RANGE if one batch of
- * 4096 rows cannot fit the budget.  COMPASS_SERIAL=1 (a debugging mode,
+ * 4096 rows cannot fit the budget.
+ * Large tables without predicates whose non-negative keys repeat (fewer
+ * values than rows) are counted first: each distinct key is then hashed
+ * once, weighted with its multiplicity (the same counters; at most 4 GiB of
+ * scratch more).  Keys are sampled and counted on the device in the same
+ * call; a column they rule out is hashed row by row.  COMPASS_SERIAL=1 (a debugging mode,
  * read at each call) builds with one chunk per group of sketch rows and a
  * single compaction workgroup, so that no two workgroups combine partial
  * counters: its results equal the default launch's bit for bit. */
@@ -579,7 +584,7 @@ compass_status compass_enumerate_greedy(int32_t n_tables, int32_t n_edges,
 /* Kernel timing for measurement: while enabled, the library records a pair
  * of HIP events on the launch stream around each kernel launch it makes.
  * compass_profile_take(name) waits for the recorded events of kernel `name`
- * ("scan_sketch", "slab_reduce", "wide_compact", "wide_hash", "fill_zero",
+ * ("scan_sketch", "count", "weighted_scan", "slab_reduce", "wide_compact", "wide_hash", "fill_zero",
  * "sort_rows", "node", "tri_order", "tri_lane", "finish", "scan2d",
  * "chain3", "agms_build", "agms_estimate", "generic"),
  * returns their count and summed elapsed milliseconds, and forgets them.

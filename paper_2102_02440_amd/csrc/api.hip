@@ -20,6 +20,7 @@
 #include "build_params.hpp"
 #include "build_plan.hpp"
 #include "compass.h"
+#include "count_params.hpp"
 #include "estimate_buffers.hpp"
 #include "estimate_params.hpp"
 #include "generic_params.hpp"
@@ -43,7 +44,12 @@ hipError_t launch_slab_reduce(const int32_t *slab, int64_t chunks,
                               int n_slices, int d, int w,
                               void *const *counters, int n_sketches,
                               int counter_bits, int accumulate,
-                              const FlushCtl &fc, hipStream_t st);
+                              const FlushCtl &fc, const CountMap &cmap,
+                              hipStream_t st);
+hipError_t launch_count_start(const ZeroSpans &z, const CountArgs &A, hipStream_t st);
+hipError_t launch_count(const CountArgs &A, int n_wg, int max_bins, int max_items,
+                        int max_stride, hipStream_t st);
+hipError_t launch_weighted_scan(const WeightedArgs &W, size_t lds, hipStream_t st);
 hipError_t launch_store_seeds(const RowSeeds *src, int n, RowSeeds *dst,
                               hipStream_t st);
 hipError_t launch_sort_rows(const SortJob *jobs, int n_jobs,
@@ -435,10 +441,193 @@ static compass_status build_two_phase(const BuildParams &base,
     {
       ProfScope ps("slab_reduce", stream);
       HIP_OK(launch_slab_reduce(wslab, pl.chunks, S, d, w, cp, n_sketches,
-                                counter_bits, 1, fc, stream));
+                                counter_bits, 1, fc, CountMap{}, stream));
     }
   }
   return COMPASS_OK;
+}
+
+// Counted build of a table without predicates (count_kernels.hip): which
+// key columns are counted, and the scratch of its kernels, laid out before
+// the slab.
+constexpr size_t kCountScratchCap = (size_t)4 << 30;
+
+struct CountedPlan {
+  CountArgs a;
+  CountTiles tiles;
+  CountMap map;
+  int max_bins = 0, max_items = 0, max_stride = 0;
+  size_t o_sg = 0, sg_bytes = 0;   // super-group totals: cleared first
+  size_t o_chunks = 0, bytes = 0;
+  std::array<size_t, 8> off[kMaxSketches];  // per column: sgtot .. exc
+};
+
+// Fills `cp` (device pointers still unset); false when no column is counted.
+static bool plan_counted(const BuildParams &base, int n_sketches, int d,
+                         int64_t n_rows, int n_cu, CountedPlan &cp) {
+  memset(&cp.a, 0, sizeof cp.a);
+  memset(&cp.map, 0, sizeof cp.map);
+  int users[kMaxSketches], first_of[kMaxSketches], n_all = 0;
+  int all_of[kMaxSketches];   // sketch -> distinct column
+  for (int s = 0; s < n_sketches; ++s) {
+    int c = 0;
+    while (c < n_all && !(base.keys[first_of[c]].col == base.keys[s].col &&
+                          base.keys[first_of[c]].dtype == base.keys[s].dtype))
+      ++c;
+    if (c == n_all) {
+      first_of[c] = s;
+      users[c] = 0;
+      ++n_all;
+    }
+    ++users[c];
+    all_of[s] = c;
+  }
+  int8_t counted[kMaxSketches];
+  CountArgs &A = cp.a;
+  for (int c = 0; c < n_all; ++c) {
+    counted[c] = -1;
+    const int bins = counted_bins(n_rows, users[c] * d);
+    if (bins < 1) continue;
+    CountCol &col = A.c[A.n_cols];
+    col.col = base.keys[first_of[c]].col;
+    col.dtype = base.keys[first_of[c]].dtype;
+    col.nbins = bins;
+    col.range = (uint32_t)bins << kCntBinBits;
+    col.rec_stride = (kCntTile + 3 * bins + 7) / 8 * 8;
+    counted[c] = (int8_t)A.n_cols++;
+  }
+  if (A.n_cols == 0) return false;
+  for (int s = 0; s < n_sketches; ++s) cp.map.col[s] = counted[all_of[s]];
+  cp.tiles = count_tiles(n_rows, A.n_cols, 2 * n_cu);
+  A.n_rows = n_rows;
+  A.n_selected = base.n_selected;
+  A.n_tiles = cp.tiles.n_tiles;
+  A.n_sg = cp.tiles.n_sg;
+  A.wg_per_sg = cp.tiles.wg_per_sg;
+  A.tiles_per_wg = cp.tiles.tiles_per_wg;
+  // about two waves of items over the columns (two workgroups per CU; bins
+  // of fewer records add items of their own): larger items leave a long
+  // last wave, smaller ones write and sum more 64 KiB parts (two columns of
+  // 36M keys: items and sums 130, 126, 123 us at 1.5, 3 and 5 shares a CU)
+  A.item_records = (int32_t)std::max<int64_t>(32768, n_rows * A.n_cols / (4 * n_cu));
+  size_t off = plan_align(sizeof(CountState) * A.n_cols);
+  auto carve = [&](size_t bytes) {
+    const size_t o = off;
+    off += plan_align(bytes);
+    return o;
+  };
+  A.max_exc = (uint32_t)(n_rows / 32);
+  cp.o_sg = off;
+  for (int c = 0; c < A.n_cols; ++c)
+    cp.off[c][0] = carve((size_t)A.n_sg * A.c[c].nbins * 4);
+  cp.sg_bytes = off - cp.o_sg;
+  cp.o_chunks = carve((size_t)n_sketches * d * 4);
+  for (int c = 0; c < A.n_cols; ++c) {
+    const CountCol &col = A.c[c];
+    // a bin of t records has at most max(1, t / T + 1 / 2) items: every one
+    // but its last holds at least an equal share
+    const int items = col.nbins * 3 / 2 + (int)(n_rows / A.item_records) + 2;
+    cp.max_items = std::max(cp.max_items, items);
+    cp.max_bins = std::max(cp.max_bins, col.nbins);
+    cp.max_stride = std::max(cp.max_stride, col.rec_stride);
+    cp.off[c][1] = carve((size_t)A.n_tiles * col.rec_stride * 2);
+    cp.off[c][2] = carve((size_t)A.n_tiles * (col.nbins + 1) * 2);
+    cp.off[c][3] = carve(sizeof(CountItem) * items);
+    cp.off[c][4] = carve(sizeof(uint2) * col.nbins);
+    cp.off[c][5] = carve((size_t)items * kCntBinKeys * 4);
+    cp.off[c][6] = carve((size_t)std::min<int64_t>(col.range, n_rows) * 8);
+    cp.off[c][7] = carve(8ull * A.max_exc);
+  }
+  cp.bytes = off;
+  return cp.bytes <= kCountScratchCap;
+}
+
+// Device pointers of a counted plan whose scratch starts at `scr`.
+static void place_counted(CountedPlan &cp, char *scr) {
+  CountArgs &A = cp.a;
+  A.st = reinterpret_cast<CountState *>(scr);
+  cp.map.st = A.st;
+  cp.map.slice_chunks = reinterpret_cast<int32_t *>(scr + cp.o_chunks);
+  for (int c = 0; c < A.n_cols; ++c) {
+    CountCol &col = A.c[c];
+    const auto &o = cp.off[c];
+    col.sgtot = reinterpret_cast<uint32_t *>(scr + o[0]);
+    col.recs = reinterpret_cast<uint16_t *>(scr + o[1]);
+    col.tab = reinterpret_cast<uint16_t *>(scr + o[2]);
+    col.items = reinterpret_cast<CountItem *>(scr + o[3]);
+    col.bin_item = reinterpret_cast<uint2 *>(scr + o[4]);
+    col.part = reinterpret_cast<int32_t *>(scr + o[5]);
+    col.keys = reinterpret_cast<uint32_t *>(scr + o[6]);
+    col.wts = reinterpret_cast<int32_t *>(col.keys) +
+              std::min<int64_t>(col.range, A.n_rows);
+    col.exc = reinterpret_cast<uint64_t *>(scr + o[7]);
+  }
+}
+
+// Counting and the weighted scan into the slab (chunk rows of n_slices x w
+// int32, max_chunks of them), after launch_count_start.
+static compass_status run_counted(const CountedPlan &cp, int32_t *slab, int max_chunks,
+                                  const compass_sketch_spec *sketches,
+                                  int n_sketches, int d, const BucketMod &bm,
+                                  int n_cu, hipStream_t stream) {
+  const CountArgs &A = cp.a;
+  {
+    ProfScope ps("count", stream);
+    HIP_OK(launch_count(A, cp.tiles.n_wg, cp.max_bins, cp.max_items,
+                        cp.max_stride, stream));
+  }
+  // slice groups: a column's slices in equal shares that fit the LDS budget
+  const int w = (int)bm.w;
+  const int per_max = std::min<int>((int)(kLdsBudget / ((size_t)w * 4)), kMaxLaunchSlices);
+  WeightedArgs W;
+  memset(&W, 0, sizeof W);
+  W.st = A.st;
+  W.slice_chunks = const_cast<int32_t *>(cp.map.slice_chunks);
+  W.slab = slab;
+  W.n_slices_total = n_sketches * d;
+  W.max_chunks = max_chunks;
+  W.bm = bm;
+  for (int c = 0; c < A.n_cols; ++c) {
+    W.keys[c] = A.c[c].keys;
+    W.wts[c] = A.c[c].wts;
+    W.exc[c] = A.c[c].exc;
+  }
+  int ls = 0, biggest = 0;
+  auto flush = [&]() -> compass_status {
+    if (W.n_groups == 0) return COMPASS_OK;
+    const size_t lds = (size_t)biggest * w * 4;
+    W.slots = n_cu * std::max(1, std::min(2, (int)((160 * 1024) / (lds + 1024))));
+    ProfScope ps("weighted_scan", stream);
+    HIP_OK(launch_weighted_scan(W, lds, stream));
+    W.n_groups = 0;
+    ls = biggest = 0;
+    return COMPASS_OK;
+  };
+  for (int c = 0; c < A.n_cols; ++c) {
+    std::vector<int> sl;
+    for (int s = 0; s < n_sketches; ++s)
+      if (cp.map.col[s] == c)
+        for (int i = 0; i < d; ++i) sl.push_back(s * d + i);
+    const int n = (int)sl.size();
+    const int groups = (n + per_max - 1) / per_max;
+    for (int g = 0; g < groups; ++g) {
+      const int a = n * g / groups, b = n * (g + 1) / groups;
+      if (W.n_groups == kMaxLaunchGroups || ls + (b - a) > kMaxLaunchSlices) {
+        const compass_status st = flush();
+        if (st != COMPASS_OK) return st;
+      }
+      W.group_begin[W.n_groups] = (int16_t)ls;
+      W.group_col[W.n_groups] = (int8_t)c;
+      for (int q = a; q < b; ++q, ++ls) {
+        const uint64_t *sd = sketches[sl[q] / d].seeds + 6 * (sl[q] % d);
+        W.seeds[ls] = RowSeeds{sd[0], sd[1], sd[2], sd[3], sd[4], sd[5]};
+        W.gs[ls] = (int16_t)sl[q];
+      }
+      biggest = std::max(biggest, b - a);
+      W.group_begin[++W.n_groups] = (int16_t)ls;
+    }
+  }
+  return flush();
 }
 
 // The pooled arena of the current device and `stream`, and its CU count.
@@ -617,20 +806,43 @@ static compass_status sketch_build_impl(
   const int64_t rows_per_chunk = fused_rows_per_chunk(n_rows, chunks, kScanTile);
   chunks = (n_rows + rows_per_chunk - 1) / rows_per_chunk;
   base.rows_per_chunk = rows_per_chunk;
-  void *slab;
-  st = ar.get((size_t)chunks * slab_row, &slab);
+  // key columns with few distinct keys for their rows are counted first and
+  // hashed once per key; the fused scan takes what the counting leaves
+  CountedPlan cp;
+  CountMap cp_map;
+  memset(&cp_map, 0, sizeof cp_map);
+  const bool counted = !ar.fixed && !serial && !sink.out && n_preds == 0 &&
+                       plan_counted(base, n_sketches, d, n_rows, n_cu, cp);
+  const size_t count_bytes = counted ? cp.bytes : 0;
+  int64_t slab_rows = chunks;
+  if (counted)
+    slab_rows = std::max<int64_t>(chunks, std::min<int64_t>(n_cu, slab_cap / slab_row));
+  void *scr;
+  st = ar.get(count_bytes + (size_t)slab_rows * slab_row, &scr);
   if (st != COMPASS_OK) return st;
-  base.slab = reinterpret_cast<int32_t *>(slab);
+  base.slab = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(scr) + count_bytes);
   base.d = d;
   base.n_slices_total = S;
-  if (zs.n > 0) {
+  if (counted) {
+    place_counted(cp, reinterpret_cast<char *>(scr));
+    zs.add(reinterpret_cast<char *>(scr) + cp.o_sg, (int64_t)cp.sg_bytes);
+    ProfScope ps("fill_zero", stream);
+    HIP_OK(launch_count_start(zs, cp.a, stream));
+  } else if (zs.n > 0) {
     ProfScope ps("fill_zero", stream);
     HIP_OK(launch_fill_zero_list(zs, stream));
   }
 
+  if (counted) {
+    st = run_counted(cp, base.slab, (int)slab_rows, sketches, n_sketches, d, base.bm,
+                     n_cu, stream);
+    if (st != COMPASS_OK) return st;
+    base.cmap = cp_map = cp.map;
+  }
+
   // launches: as many whole groups as the kernel-argument seed table holds
   int slice = 0;
-  bool first = true;
+  bool first = !counted;   // the counting adds the table's rows by itself
   while (slice < S) {
     BuildParams P = base;
     int ls = 0, ng = 0;
@@ -671,7 +883,7 @@ static compass_status sketch_build_impl(
     memset(&none, 0, sizeof none);
     ProfScope ps("slab_reduce", stream);
     HIP_OK(launch_slab_reduce(base.slab, chunks, S, d, w, cp, n_sketches,
-                              counter_bits, accumulate, none, stream));
+                              counter_bits, accumulate, none, cp_map, stream));
   }
   return COMPASS_OK;
 }

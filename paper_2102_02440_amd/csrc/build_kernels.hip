@@ -53,6 +53,10 @@ struct ParamJob {
   __device__ void *counters(int s) const { return P.counters[s]; }
 };
 
+// kSome: a counted build's launch, which hashes the slices the weighted scan
+// has not taken (an instance of its own: the test per slice costs the plain
+// scan 1.5%).
+template <bool kSome>
 __global__ __launch_bounds__(kBuildThreads) void scan_sketch_kernel(
     const BuildParams P) {
   extern __shared__ int32_t lds[];
@@ -73,6 +77,12 @@ __global__ __launch_bounds__(kBuildThreads) void scan_sketch_kernel(
   const int se = P.group_begin[gi + 1];
   const int ns = se - sb;
   const int w = (int)P.bm.w;
+  uint64_t live = 0;
+  if (kSome) {
+    for (int l = 0; l < ns; ++l)
+      live |= P.cmap.counted(job.slice_sketch(sb + l)) ? 0ull : 1ull << l;
+    if (!live) return;
+  }
   int32_t *cnt = lds;                       // ns * w partial counters
   int32_t *queue = lds + (size_t)ns * w;    // kScanTile row offsets (with
                                             // predicates only)
@@ -84,12 +94,13 @@ __global__ __launch_bounds__(kBuildThreads) void scan_sketch_kernel(
   RowSink sink = P.sink;
   if (gi != 0) sink.out = nullptr;  // one slice group writes the rows
   const uint64_t sel =
-      scan_rows<ParamJob, kScanRowsPerThread>(job, row0, row1, sb, se, cnt,
-                                              queue, &s_qn, sink);
+      scan_rows<ParamJob, kScanRowsPerThread, kSome>(job, row0, row1, sb, se, cnt,
+                                                     queue, &s_qn, sink, live);
   // partial counters of this chunk -> its slab rows (plain coalesced
   // stores; the reduction kernel sums the chunks in a fixed order)
   const size_t S = (size_t)P.n_slices_total;
   for (int l = 0; l < ns; ++l) {
+    if (kSome && !((live >> l) & 1ull)) continue;
     const int sl = sb + l;
     const size_t gs = (size_t)(P.slice_base + sl);
     int32_t *dst = P.slab + ((size_t)chunk * S + gs) * w;
@@ -403,7 +414,8 @@ __global__ void slab_reduce_kernel(const int32_t *__restrict__ slab,
                                    int64_t chunks, int32_t n_slices, int32_t d,
                                    int32_t w, CounterList cl,
                                    int32_t counter_bits, int32_t accumulate,
-                                   FlushCtl fc, int32_t vec4) {
+                                   FlushCtl fc, CountMap cmap, int32_t vec4) {
+  const int64_t scan_chunks = chunks;
   // two-phase builds: a flush reduces only the chunks wide_hash_kernel
   // filled, and its last workgroup empties the survivor buffer
   if (fc.count) {
@@ -419,6 +431,11 @@ __global__ void slab_reduce_kernel(const int32_t *__restrict__ slab,
     const int4 *slab4 = reinterpret_cast<const int4 *>(slab);
     for (int64_t k4 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
          k4 < total4; k4 += (int64_t)gridDim.x * blockDim.x) {
+      const int64_t k = 4 * k4;
+      const int gs = (int)(k / w);
+      const int j = (int)(k - (int64_t)gs * w);
+      const int s = gs / d, row = gs - s * d;
+      if (cmap.st) chunks = cmap.counted(s) ? cmap.slice_chunks[gs] : scan_chunks;
       int64_t a[4] = {0, 0, 0, 0};
       int64_t c = 0;
       for (; c + 8 <= chunks; c += 8) {
@@ -440,10 +457,6 @@ __global__ void slab_reduce_kernel(const int32_t *__restrict__ slab,
         a[2] += v.z;
         a[3] += v.w;
       }
-      const int64_t k = 4 * k4;
-      const int gs = (int)(k / w);
-      const int j = (int)(k - (int64_t)gs * w);
-      const int s = gs / d, row = gs - s * d;
       const size_t idx = (size_t)row * w + j;  // a multiple of 4
       if (counter_bits == 32) {
         int4 *g = reinterpret_cast<int4 *>(reinterpret_cast<int32_t *>(cl.p[s]) + idx);
@@ -468,6 +481,10 @@ __global__ void slab_reduce_kernel(const int32_t *__restrict__ slab,
   }
   for (int64_t k = vec4 ? total : blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
        k < total; k += (int64_t)gridDim.x * blockDim.x) {
+    const int gs = (int)(k / w);
+    const int j = (int)(k - (int64_t)gs * w);
+    const int s = gs / d, row = gs - s * d;
+    if (cmap.st) chunks = cmap.counted(s) ? cmap.slice_chunks[gs] : scan_chunks;
     // eight chunk rows in flight per lane
     int64_t a8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     int64_t c = 0;
@@ -479,9 +496,6 @@ __global__ void slab_reduce_kernel(const int32_t *__restrict__ slab,
     int64_t acc = 0;
 #pragma unroll
     for (int u = 0; u < 8; ++u) acc += a8[u];
-    const int gs = (int)(k / w);
-    const int j = (int)(k - (int64_t)gs * w);
-    const int s = gs / d, row = gs - s * d;
     const size_t idx = (size_t)row * w + j;
     if (counter_bits == 32) {
       int32_t *g = reinterpret_cast<int32_t *>(cl.p[s]);
@@ -510,7 +524,8 @@ hipError_t launch_slab_reduce(const int32_t *slab, int64_t chunks,
                               int n_slices, int d, int w,
                               void *const *counters, int n_sketches,
                               int counter_bits, int accumulate,
-                              const FlushCtl &fc, hipStream_t st) {
+                              const FlushCtl &fc, const CountMap &cmap,
+                              hipStream_t st) {
   CounterList cl;
   // 16-byte vector path: rows of a multiple of 4 counters, every counter
   // array 16-byte aligned (the slab is)
@@ -525,7 +540,7 @@ hipError_t launch_slab_reduce(const int32_t *slab, int64_t chunks,
   if (blocks < 1) blocks = 1;
   hipLaunchKernelGGL(slab_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0,
                      st, slab, chunks, n_slices, d, w, cl, counter_bits,
-                     accumulate, fc, vec4);
+                     accumulate, fc, cmap, vec4);
   return hipGetLastError();
 }
 
@@ -594,9 +609,12 @@ hipError_t launch_scan_sketch(const BuildParams &P, int n_blocks,
                               size_t lds_bytes, hipStream_t st) {
   // P.n_blocks pairs, padded to whole rounds of the XCDs
   const int grid = (n_blocks + kXcds - 1) / kXcds * kXcds;
-  hipLaunchKernelGGL(scan_sketch_kernel,
-                     dim3((unsigned)grid), dim3(kBuildThreads), lds_bytes,
-                     st, P);
+  if (P.cmap.st)
+    hipLaunchKernelGGL(scan_sketch_kernel<true>, dim3((unsigned)grid),
+                       dim3(kBuildThreads), lds_bytes, st, P);
+  else
+    hipLaunchKernelGGL(scan_sketch_kernel<false>, dim3((unsigned)grid),
+                       dim3(kBuildThreads), lds_bytes, st, P);
   return hipGetLastError();
 }
 

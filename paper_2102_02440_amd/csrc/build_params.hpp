@@ -68,6 +68,27 @@ struct ZeroSpans {
   }
 };
 
+// Device state of one counted key column (count_kernels.hip), zeroed at the
+// start of a call.
+struct CountState {
+  uint32_t bad;      // too many keys lie outside the counted range: the
+                     // column is hashed row by row
+  uint32_t n_keys;   // distinct keys listed so far
+  uint32_t n_items;  // counting items planned
+  uint32_t n_exc;    // keys outside the range, listed one by one
+};
+
+// Which sketches a counted build takes from the weighted scan: those whose
+// column (an index into `st`, -1: not counted) is not bad.
+struct CountMap {
+  const CountState *st;          // nullptr: nothing is counted
+  const int32_t *slice_chunks;   // slab rows of a counted slice
+  int8_t col[kMaxSketches];
+  __device__ bool counted(int s) const {
+    return st && col[s] >= 0 && !st[col[s]].bad;
+  }
+};
+
 struct BuildParams {
   int64_t n_rows;
   int64_t rows_per_chunk;
@@ -91,6 +112,7 @@ struct BuildParams {
   int32_t group_begin[kMaxLaunchGroups + 1];  // 32-bit: scalar loads
   RowSeeds seeds[kMaxLaunchSlices];
   RowSink sink;         // written by the workgroups of slice group 0 only
+  CountMap cmap;
 };
 
 static_assert(sizeof(BuildParams) <= 4096, "kernel arguments must stay small");
