@@ -72,8 +72,8 @@ hipError_t launch_tri_lane(const TriTask *tasks, int n, const TriGroup *groups,
 hipError_t launch_gen_contract(const GenArgs &A, const EstBuffers &B,
                                int n_blocks, int fp64, hipStream_t st);
 hipError_t launch_finish(const SubplanTask *sps, int n, const EstBuffers &B,
-                         const double *approx, uint64_t *row_est, double *est,
-                         int32_t *flags, int32_t n_tables, hipStream_t st);
+                         uint64_t *row_est, double *est, int32_t *flags,
+                         int32_t n_tables, hipStream_t st);
 hipError_t launch_scan2d(const BuildParams &P, const KdDims &kx, int n_blocks,
                          hipStream_t st);
 hipError_t launch_tensor_level(const TensorArgs &A, int n_tasks, int max_blocks,
@@ -1018,8 +1018,10 @@ struct Planner {
   int64_t glists_len = 0;             // merged list entries, all blocks
   int64_t gmsg_len = 0;               // values (16 bytes each)
   int n_approx_slots = 0;
-  // message tasks by subtree: shared by every sub-plan that needs them
-  std::map<std::string, int> msg_task;
+  // message tasks by subtree: shared by every sub-plan that needs them; and
+  // their twins in double, shared by the tree sub-plans
+  std::map<std::string, int> msg_task, fmsg_task;
+  int n_fmsg_slots = 0;
 
   int side_of(int table, int e) const {
     return 2 * e + (g->edge_u[e] == table ? 0 : 1);
@@ -1373,11 +1375,27 @@ static compass_status plan_subplan(Planner &pl, uint64_t mask, int spi) {
     // counters (slot -1 - side: read in place, no task).  A message whose
     // subtree (tables, edges, cut edges) another sub-plan already planned
     // is the same array: its slots are shared and no task is added.
-    std::vector<int> msg_slot(nn, -1), cmsg_slot(nn, -1);
+    std::vector<int> msg_slot(nn, -1), cmsg_slot(nn, -1), fmsg_slot(nn, -1);
+    std::vector<uint64_t> sub_tables(nn, 0);
     std::vector<std::string> key(nn);
+    // the twin in double of a tree sub-plan's node: the same lists, its own
+    // message (or approximate root value) slots
+    auto add_twin = [&](int a, NodeTask T, int level) {
+      T.fp = 1;
+      T.guard.n = 0;
+      T.tables = sub_tables[a];
+      T.msg_slot = fmsg_slot[a];
+      for (int c = 0; c < T.m; ++c) T.child_msg[c] = fmsg_slot[nodes[a].children[c]];
+      if (a == root) T.out_slot = sp.approx_slot;
+      pl.tasks.push_back(T);
+      pl.task_level.push_back(level);
+    };
     for (int k = nn - 1; k >= 0; --k) {
       const int a = o.order[k];
       PlanNode &nd = nodes[a];
+      sub_tables[a] |= 1ull << nd.table;
+      for (int c : nd.children) sub_tables[a] |= sub_tables[c];
+      bool twin_only = false;   // the 128-bit message is planned already
       if (a != root) {
         std::vector<std::string> ck;
         for (size_t c = 0; c < nd.children.size(); ++c) ck.push_back(key[nd.children[c]]);
@@ -1387,7 +1405,7 @@ static compass_status plan_subplan(Planner &pl, uint64_t mask, int spi) {
         for (auto &x : ck) key[a] += x;
         key[a] += ")";
         if (nd.children.empty()) {
-          msg_slot[a] = -1 - pl.side_of(nd.table, nd.parent_edge);
+          msg_slot[a] = fmsg_slot[a] = -1 - pl.side_of(nd.table, nd.parent_edge);
           if (nd.cut_edge >= 0) cmsg_slot[a] = -1 - pl.side_of(nd.table, nd.cut_edge);
           continue;
         }
@@ -1398,11 +1416,22 @@ static compass_status plan_subplan(Planner &pl, uint64_t mask, int spi) {
           cmsg_slot[a] = S.cmsg_slot;
           // shared by rootings of different guards: always computed
           if (memcmp(&S.guard, &gd, sizeof(gd)) != 0) S.guard.n = 0;
-          continue;
+          if (cut_e >= 0) continue;
+          auto ft = pl.fmsg_task.find(key[a]);
+          if (ft != pl.fmsg_task.end()) {
+            fmsg_slot[a] = ft->second;
+            continue;
+          }
+          twin_only = true;
+        } else {
+          msg_slot[a] = pl.n_msg_slots++;
+          if (nd.cut_edge >= 0) cmsg_slot[a] = pl.n_msg_slots++;
+          pl.msg_task[key[a]] = (int)pl.tasks.size();
         }
-        msg_slot[a] = pl.n_msg_slots++;
-        if (nd.cut_edge >= 0) cmsg_slot[a] = pl.n_msg_slots++;
-        pl.msg_task[key[a]] = (int)pl.tasks.size();
+        if (cut_e < 0) {
+          fmsg_slot[a] = pl.n_fmsg_slots++;
+          pl.fmsg_task[key[a]] = fmsg_slot[a];
+        }
       }
       NodeTask T;
       memset(&T, 0, sizeof(T));
@@ -1442,6 +1471,8 @@ static compass_status plan_subplan(Planner &pl, uint64_t mask, int spi) {
         T.out_slot = pl.n_x_slots++;
         sp.type = kSpTree;
         sp.x_slot = T.out_slot;
+        sp.approx_slot = pl.n_approx_slots++;
+        sp.n_approx = 1;
       } else {
         T.mode = kModeTriRootPrep;
         T.out_slot = pl.n_prep_slots++;
@@ -1500,8 +1531,11 @@ static compass_status plan_subplan(Planner &pl, uint64_t mask, int spi) {
                               tr.cut_child[1]});
       }
       if (T.m > 0) pl.Lmax = std::max(pl.Lmax, nl * pl.w);
-      pl.tasks.push_back(T);
-      pl.task_level.push_back(nd.height);
+      if (!twin_only) {
+        pl.tasks.push_back(T);
+        pl.task_level.push_back(nd.height);
+      }
+      if (cut_e < 0) add_twin(a, T, nd.height);
     }
   }
   pl.sps.push_back(sp);
@@ -1560,10 +1594,11 @@ extern "C" compass_status compass_estimate(const compass_join_graph *g,
     if (s != COMPASS_OK) return s;
   }
   // an fp64 evaluation of every multi-table sub-plan, run on the device
-  // only when its 128-bit values cannot be certified
+  // only when its 128-bit values cannot be certified (tree sub-plans have
+  // their nodes' twins in double)
   for (int i = 0; i < n_subplans; ++i) {
     SubplanTask &sp = pl.sps[i];
-    if (sp.n_tables < 2 || sp.type == kSpUnsupported) continue;
+    if (sp.n_tables < 2 || sp.type == kSpUnsupported || sp.type == kSpTree) continue;
     int slot = 0, n = 0;
     if (plan_generic(pl, masks[i], i, true, &slot, &n)) {
       sp.approx_slot = slot;
@@ -1650,8 +1685,13 @@ extern "C" compass_status compass_estimate(const compass_join_graph *g,
   }
   const size_t o_tgroups = carve(sizeof(TriGroup) * std::max<size_t>(1, tgroups.size()));
   const size_t o_sps = carve(sizeof(SubplanTask) * pl.sps.size());
+  const size_t o_gnodes = carve(sizeof(GenNode) * std::max<size_t>(1, pl.gnodes.size()));
+  const size_t o_gplans = carve(sizeof(GenPlan) * std::max<size_t>(1, pl.gplans.size()));
+  const size_t o_gblk0 = carve(sizeof(GenBlock) * std::max<size_t>(1, pl.gblocks[0].size()));
+  const size_t o_gblk1 = carve(sizeof(GenBlock) * std::max<size_t>(1, pl.gblocks[1].size()));
   const size_t o_sorted = carve(sizeof(uint64_t) * 2 * g->n_edges * d * (size_t)w);
   const size_t o_msg = carve(16ull * pl.n_msg_slots * d * (size_t)w);
+  const size_t o_fmsg = carve(8ull * pl.n_fmsg_slots * d * (size_t)w);
   const size_t o_merged = carve(4ull * max_level_tasks * d * (size_t)std::max(1, pl.Lmax));
   const size_t o_nrec = carve(sizeof(NodeRec) * max_level_tasks * d *
                               (size_t)std::max(1, pl.Lmax));
@@ -1671,10 +1711,6 @@ extern "C" compass_status compass_estimate(const compass_join_graph *g,
   const size_t o_tpiece = carve(sizeof(TriPiece) * np * d * (size_t)pcap);
   const size_t o_tsegp = carve(sizeof(int32_t) * np * d * (kFastSegs + 1));
   const size_t o_part = carve(16ull * std::max(1, pl.n_partial_slots) * d);
-  const size_t o_gnodes = carve(sizeof(GenNode) * std::max<size_t>(1, pl.gnodes.size()));
-  const size_t o_gplans = carve(sizeof(GenPlan) * std::max<size_t>(1, pl.gplans.size()));
-  const size_t o_gblk0 = carve(sizeof(GenBlock) * std::max<size_t>(1, pl.gblocks[0].size()));
-  const size_t o_gblk1 = carve(sizeof(GenBlock) * std::max<size_t>(1, pl.gblocks[1].size()));
   const size_t o_glists = carve(4ull * std::max<int64_t>(1, pl.glists_len));
   const size_t o_gmsg = carve(16ull * std::max<int64_t>(1, pl.gmsg_len));
   const size_t o_approx = carve(8ull * std::max(1, pl.n_approx_slots) * d);
@@ -1695,23 +1731,16 @@ extern "C" compass_status compass_estimate(const compass_join_graph *g,
   if (!tgroups.empty())
     memcpy(host.data() + o_tgroups, tgroups.data(), sizeof(TriGroup) * tgroups.size());
   memcpy(host.data() + o_sps, pl.sps.data(), sizeof(SubplanTask) * pl.sps.size());
+  if (!pl.gplans.empty()) {
+    memcpy(host.data() + o_gnodes, pl.gnodes.data(), sizeof(GenNode) * pl.gnodes.size());
+    memcpy(host.data() + o_gplans, pl.gplans.data(), sizeof(GenPlan) * pl.gplans.size());
+    for (int f = 0; f < 2; ++f)
+      if (!pl.gblocks[f].empty())
+        memcpy(host.data() + (f ? o_gblk1 : o_gblk0), pl.gblocks[f].data(),
+               sizeof(GenBlock) * pl.gblocks[f].size());
+  }
   st = upload(ds, base, host.data(), o_sorted, stream);
   if (st != COMPASS_OK) return st;
-  if (!pl.gplans.empty()) {
-    // the generic plans' tables (between o_gnodes and o_glists)
-    std::vector<char> gh(o_glists - o_gnodes, 0);
-    memcpy(gh.data(), pl.gnodes.data(), sizeof(GenNode) * pl.gnodes.size());
-    memcpy(gh.data() + (o_gplans - o_gnodes), pl.gplans.data(),
-           sizeof(GenPlan) * pl.gplans.size());
-    if (!pl.gblocks[0].empty())
-      memcpy(gh.data() + (o_gblk0 - o_gnodes), pl.gblocks[0].data(),
-             sizeof(GenBlock) * pl.gblocks[0].size());
-    if (!pl.gblocks[1].empty())
-      memcpy(gh.data() + (o_gblk1 - o_gnodes), pl.gblocks[1].data(),
-             sizeof(GenBlock) * pl.gblocks[1].size());
-    st = upload(ds, base + o_gnodes, gh.data(), gh.size(), stream);
-    if (st != COMPASS_OK) return st;
-  }
 
   EstBuffers B;
   memset(&B, 0, sizeof(B));
@@ -1719,6 +1748,8 @@ extern "C" compass_status compass_estimate(const compass_join_graph *g,
   B.n_sel = g->n_selected;
   B.sorted = reinterpret_cast<const uint64_t *>(base + o_sorted);
   B.msg = reinterpret_cast<u128 *>(base + o_msg);
+  B.fmsg = reinterpret_cast<double *>(base + o_fmsg);
+  B.approx = reinterpret_cast<double *>(base + o_approx);
   B.merged = reinterpret_cast<uint32_t *>(base + o_merged);
   B.nrec = reinterpret_cast<NodeRec *>(base + o_nrec);
   B.n1tot = reinterpret_cast<u128 *>(base + o_n1tot);
@@ -1747,6 +1778,10 @@ extern "C" compass_status compass_estimate(const compass_join_graph *g,
     R.tris = reinterpret_cast<TriTask *>(base + o_tris);
     R.n = (int)flat.size();
     R.n_tri = (int)pl.tris.size();
+    R.sps = reinterpret_cast<const SubplanTask *>(base + o_sps);
+    R.n_sps = (int)pl.sps.size();
+    R.n_tables = g->n_tables;
+    for (const NodeTask &t : flat) R.any_fp |= t.fp;
     ProfScope ps("sort_rows", stream);
     HIP_OK(launch_sort_rows(reinterpret_cast<const SortJob *>(base + o_jobs),
                             (int)sort_jobs.size(), R, B, stream));
@@ -1808,7 +1843,7 @@ extern "C" compass_status compass_estimate(const compass_join_graph *g,
     A.lists = reinterpret_cast<uint32_t *>(base + o_glists);
     A.msg = base + o_gmsg;
     A.partial = B.partial;
-    A.approx = reinterpret_cast<double *>(base + o_approx);
+    A.approx = B.approx;
     A.sps = reinterpret_cast<const SubplanTask *>(base + o_sps);
     A.n_tables = g->n_tables;
     ProfScope ps("generic", stream);
@@ -1821,7 +1856,6 @@ extern "C" compass_status compass_estimate(const compass_join_graph *g,
     ProfScope ps("finish", stream);
     HIP_OK(launch_finish(reinterpret_cast<const SubplanTask *>(base + o_sps),
                          (int)pl.sps.size(), B,
-                         reinterpret_cast<const double *>(base + o_approx),
                          reinterpret_cast<uint64_t *>(row_est), est, flags,
                          g->n_tables, stream));
   }

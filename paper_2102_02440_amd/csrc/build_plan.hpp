@@ -119,8 +119,8 @@ constexpr int kCntMaxSg = 64;
 // partition and counting passes, which cost about as much as kCntRowCost
 // updates per row: 3.3 ns per 1000 rows of a column against 1.6 ns per 1000
 // updates is 2.1, taken with a margin for clustered keys and narrow tables.
-// Below kCntMinUpdates the launches eat the gain: 63M updates of 4.5M rows
-// take 108 us counted and 146 us hashed row by row, 25M about 70 either way.
+// Below kCntMinUpdates the seven launches eat the gain: 63M updates of 4.5M
+// rows take 108 us counted and 146 us hashed row by row.
 constexpr double kCntRowCost = 3.5;
 constexpr double kCntMinUpdates = 5.0e7;   // below: launches would not pay
 inline int counted_bins(int64_t n_rows, int slices) {

@@ -52,7 +52,8 @@ struct TriPiece {
 // One element of a node's merged list, gathered once by the merge so that
 // the node's sweeps read consecutive records (32 bytes).
 struct NodeRec {
-  u128 mu;        // the child's message at the bucket (child lists only)
+  u128 mu;        // the child's message at the bucket (child lists only; a
+                  // twin in double: the double's bits)
   int64_t v;      // the node's counter at the bucket
   uint32_t aj;    // list << 16 | bucket
   uint32_t pad;
@@ -63,6 +64,8 @@ struct EstBuffers {
   const int64_t *n_sel;       // [n_tables]
   const uint64_t *sorted;     // [side][row][w] keys (|v| << 16 | j)
   u128 *msg;                  // [slot][row][w]
+  double *fmsg;               // [slot][row][w] messages of the twins in double
+  double *approx;             // [slot][row] fp64 row values
   uint32_t *merged;           // [scratch slot][row][Lmax]
   NodeRec *nrec;              // [scratch slot][row][Lmax]
   u128 *n1tot;                // [scratch slot][row][2 * kN1MaxChunks]

@@ -80,6 +80,66 @@ __device__ __forceinline__ u128 child_msg_at(const EstBuffers &B, int slot,
   return s64_to_u128(counter_at(B, -1 - slot, row, j));
 }
 
+// The two arithmetics of the tree messages: exact 128-bit two's complement,
+// and double for the twins (sub-plans whose 128-bit values may wrap).
+template <class T>
+struct Num;
+template <>
+struct Num<u128> {
+  static __device__ __forceinline__ u128 of(int64_t v) { return s64_to_u128(v); }
+  static __device__ __forceinline__ u128 mul(u128 a, u128 b) { return mul_u128(a, b); }
+  static __device__ __forceinline__ u128 muls(int64_t v, u128 b) { return mul_s64_u128(v, b); }
+  static __device__ __forceinline__ u128 rec(const NodeRec &r) { return r.mu; }
+  static __device__ __forceinline__ u128 child(const EstBuffers &B, int slot, int row, int j) {
+    return child_msg_at(B, slot, row, j);
+  }
+  static __device__ __forceinline__ u128 *out(const EstBuffers &B, int slot, int row) {
+    return msg_of(B, slot, row);
+  }
+  static __device__ __forceinline__ u128 *root(const EstBuffers &B, int slot, int row) {
+    return B.xout + (size_t)slot * B.d + row;
+  }
+  template <bool kDown>
+  static __device__ __forceinline__ u128 shfl(u128 v, int off) {
+    u128 r = 0;
+#pragma unroll
+    for (int k = 3; k >= 0; --k) {
+      const int x = (int)(uint32_t)(v >> (32 * k));
+      r = (r << 32) | (uint32_t)(kDown ? __shfl_down(x, off) : __shfl_up(x, off));
+    }
+    return r;
+  }
+};
+template <>
+struct Num<double> {
+  static __device__ __forceinline__ double of(int64_t v) { return (double)v; }
+  static __device__ __forceinline__ double mul(double a, double b) { return a * b; }
+  static __device__ __forceinline__ double muls(int64_t v, double b) { return (double)v * b; }
+  static __device__ __forceinline__ double rec(const NodeRec &r) {
+    return __longlong_as_double((long long)(uint64_t)r.mu);
+  }
+  static __device__ __forceinline__ double child(const EstBuffers &B, int slot, int row, int j) {
+    if (slot >= 0) return B.fmsg[((size_t)slot * B.d + row) * B.w + j];
+    return (double)counter_at(B, -1 - slot, row, j);
+  }
+  static __device__ __forceinline__ double *out(const EstBuffers &B, int slot, int row) {
+    return B.fmsg + ((size_t)slot * B.d + row) * B.w;
+  }
+  static __device__ __forceinline__ double *root(const EstBuffers &B, int slot, int row) {
+    return B.approx + (size_t)slot * B.d + row;
+  }
+  template <bool kDown>
+  static __device__ __forceinline__ double shfl(double v, int off) {
+    return kDown ? __shfl_down(v, off) : __shfl_up(v, off);
+  }
+};
+
+// the message word of a merged record: 128-bit, or a double's bits
+__device__ __forceinline__ u128 rec_msg(const EstBuffers &B, int fp, int slot, int row, int j) {
+  if (fp) return (u128)(uint64_t)__double_as_longlong(Num<double>::child(B, slot, row, j));
+  return child_msg_at(B, slot, row, j);
+}
+
 // number of keys < thr in a sorted array
 __device__ __forceinline__ int lower_bound_u64(const uint64_t *a, int n,
                                                uint64_t thr) {
@@ -169,7 +229,8 @@ __device__ __forceinline__ uint64_t abs_u64(int64_t v) {
 // fields, two per 32-bit word, wave scans by DPP row shifts and
 // broadcasts, then over the waves), and each key goes to its digit's base
 // plus the count of equal digits before it.
-__device__ void resolve_task(const ResolveArgs &R, int i, const EstBuffers &B);
+__device__ void resolve_block(const ResolveArgs &R, int block, const EstBuffers &B,
+                              uint64_t *lds);
 
 // inclusive scan over the 64 lanes of a wave (32-bit words of two 16-bit
 // fields that never carry into each other)
@@ -195,8 +256,9 @@ __device__ __forceinline__ uint32_t nibbles_to_word(uint64_t c, int k) {
 template <int KPT>  // keys per thread at most (8 or kSortKpt)
 __global__ __launch_bounds__(kSortThreads) void sort_rows_kernel(
     const SortJob *jobs, EstBuffers B, int n_pairs, ResolveArgs R) {
+  extern __shared__ __align__(16) uint64_t sk[];
   if ((int)blockIdx.x >= n_pairs) {
-    resolve_task(R, ((int)blockIdx.x - n_pairs) * kSortThreads + (int)threadIdx.x, B);
+    resolve_block(R, (int)blockIdx.x - n_pairs, B, sk);
     return;
   }
   // LDS: the keys by position, one pad entry after every 16 so that the
@@ -206,7 +268,6 @@ __global__ __launch_bounds__(kSortThreads) void sort_rows_kernel(
   // the waves' digit bases.  The largest rows (KPT = 16) fill the LDS with
   // the keys unpadded and the starts; their scratch and bases take the
   // keys' space before each scatter.
-  extern __shared__ __align__(16) uint64_t sk[];
   constexpr int kWaves = kSortThreads / 64;
   const int w = B.w;
   const int kpt = (w + kSortThreads - 1) / kSortThreads;  // uniform, <= KPT
@@ -344,26 +405,30 @@ __global__ __launch_bounds__(kSortThreads) void sort_rows_kernel(
 }
 
 // ---------------------------------------------------------------------
-// block scans over kNodeThreads 128-bit values
+// block scans over kNodeThreads values
 // ---------------------------------------------------------------------
-__device__ u128 block_scan_incl(u128 v, u128 *sh, bool suffix) {
-  const int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-  for (int off = 1; off < kNodeThreads; off <<= 1) {
-    u128 add = 0;
-    if (suffix) {
-      if (t + off < kNodeThreads) add = sh[t + off];
-    } else {
-      if (t >= off) add = sh[t - off];
-    }
-    __syncthreads();
-    sh[t] += add;
-    __syncthreads();
+// Inclusive prefix (kSuffix: suffix) sums: shuffles within the waves, then
+// the earlier (later) waves' totals from LDS, one word per wave.  (A barrier
+// per doubling over all lanes, as first written, took half of node_kernel's
+// time: the three-child nodes of an eight-table tree 83 us a level.)
+template <bool kSuffix, class T>
+__device__ __forceinline__ T block_scan_incl(T v, T *sh) {
+  constexpr int kW = kNodeThreads / 64;
+  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const T y = Num<T>::template shfl<kSuffix>(v, off);
+    if (kSuffix ? lane + off < 64 : lane >= off) v += y;
   }
-  const u128 r = sh[t];
+  if (lane == (kSuffix ? 0 : 63)) sh[wave] = v;
   __syncthreads();
-  return r;
+  T add = 0;
+  for (int k = 0; k < kW; ++k) {
+    const T y = sh[k];
+    if (kSuffix ? k > wave : k < wave) add += y;
+  }
+  __syncthreads();   // sh is reused
+  return v + add;
 }
 
 struct ListRef {
@@ -487,7 +552,7 @@ __global__ __launch_bounds__(kMergeThreads) void node_merge_kernel(
 #pragma unroll
       for (int u = 0; u < kMergeU; ++u) {
         r[u].v = counter_at(B, s_side[a[u]], row, (int)j[u]);
-        r[u].mu = a[u] < m ? child_msg_at(B, s_msg[a[u]], row, (int)j[u]) : (u128)0;
+        r[u].mu = a[u] < m ? rec_msg(B, T.guard.on & kOnDouble, s_msg[a[u]], row, (int)j[u]) : (u128)0;
         r[u].aj = ((uint32_t)a[u] << 16) | j[u];
         r[u].pad = 0;
       }
@@ -513,7 +578,7 @@ __global__ __launch_bounds__(kMergeThreads) void node_merge_kernel(
       }
       NodeRec r;
       r.v = counter_at(B, s_side[a], row, (int)j);
-      r.mu = a < m ? child_msg_at(B, s_msg[a], row, (int)j) : (u128)0;
+      r.mu = a < m ? rec_msg(B, T.guard.on & kOnDouble, s_msg[a], row, (int)j) : (u128)0;
       r.aj = ((uint32_t)a << 16) | j;
       r.pad = 0;
       merged[pos] = r.aj;
@@ -523,13 +588,13 @@ __global__ __launch_bounds__(kMergeThreads) void node_merge_kernel(
 }
 
 // product of the A of every child but `a` (a >= M: of every child)
-template <int M>
-__device__ __forceinline__ u128 times_others(u128 t, const u128 *A, int a) {
-  if (M == 1) return a >= M ? mul_u128(t, A[0]) : t;
-  if (M == 2 && a < M) return mul_u128(t, a ? A[0] : A[1]);
+template <int M, class T>
+__device__ __forceinline__ T times_others(T t, const T *A, int a) {
+  if (M == 1) return a >= M ? Num<T>::mul(t, A[0]) : t;
+  if (M == 2 && a < M) return Num<T>::mul(t, a ? A[0] : A[1]);
 #pragma unroll
   for (int c = 0; c < M; ++c)
-    if (c != a) t = mul_u128(t, A[c]);
+    if (c != a) t = Num<T>::mul(t, A[c]);
   return t;
 }
 
@@ -537,9 +602,10 @@ __device__ __forceinline__ u128 times_others(u128 t, const u128 *A, int a) {
 // thread taking a contiguous segment: the segment totals of every child's
 // messages (suffix-scanned into A at the segment start), the running term
 // sum G (prefix-scanned), and the emitted message and cut constants.
-template <int M>
+template <int M, class N>
 __device__ void node_sweeps(const NodeTask &T, const NodeRec *rec, int L,
-                            int row, const EstBuffers &B, u128 *sh) {
+                            int row, const EstBuffers &B, N *sh) {
+  using Op = Num<N>;
   // records loaded together (fewer with more children: registers)
   constexpr int kSweepU = M <= 2 ? 4 : (M == 3 ? 2 : 1);
   const int has_parent = T.parent_side >= 0;
@@ -547,7 +613,7 @@ __device__ void node_sweeps(const NodeTask &T, const NodeRec *rec, int L,
   const int s0 = min(L, (int)threadIdx.x * seg);
   const int s1 = min(L, s0 + seg);
 
-  u128 tot[M];
+  N tot[M];
 #pragma unroll
   for (int c = 0; c < M; ++c) tot[c] = 0;
   for (int p0 = s0; p0 < s1; p0 += kSweepU) {
@@ -561,17 +627,17 @@ __device__ void node_sweeps(const NodeTask &T, const NodeRec *rec, int L,
       const int a = (int)(rr[u].aj >> 16);
 #pragma unroll
       for (int c = 0; c < M; ++c)
-        if (c == a) tot[c] += rr[u].mu;
+        if (c == a) tot[c] += Op::rec(rr[u]);
     }
   }
-  u128 A0[M];  // A at the start of my segment (inclusive)
+  N A0[M];  // A at the start of my segment (inclusive)
 #pragma unroll
-  for (int c = 0; c < M; ++c) A0[c] = block_scan_incl(tot[c], sh, true);
+  for (int c = 0; c < M; ++c) A0[c] = block_scan_incl<true>(tot[c], sh);
 
-  u128 A[M];
+  N A[M];
 #pragma unroll
   for (int c = 0; c < M; ++c) A[c] = A0[c];
-  u128 gl = 0;
+  N gl = 0;
   for (int p0 = s0; p0 < s1; p0 += kSweepU) {
     NodeRec rr[kSweepU];
 #pragma unroll
@@ -583,26 +649,26 @@ __device__ void node_sweeps(const NodeTask &T, const NodeRec *rec, int L,
       const NodeRec &r = rr[u];
       const int a = (int)(r.aj >> 16);
       if (a >= M) continue;
-      gl += times_others<M>(mul_s64_u128(r.v, r.mu), A, a);
+      gl += times_others<M>(Op::muls(r.v, Op::rec(r)), A, a);
 #pragma unroll
       for (int c = 0; c < M; ++c)
-        if (c == a) A[c] -= r.mu;
+        if (c == a) A[c] -= Op::rec(r);
     }
   }
-  const u128 gincl = block_scan_incl(gl, sh, false);
+  const N gincl = block_scan_incl<false>(gl, sh);
 
   if (T.mode == kModeTreeRoot) {
     if (threadIdx.x == kNodeThreads - 1)
-      B.xout[(size_t)T.out_slot * B.d + row] = gincl;
+      *Op::root(B, T.out_slot, row) = gincl;
     return;
   }
 
   // emit the message (parent list) and cut constants (cut list)
-  u128 G = gincl - gl;
+  N G = gincl - gl;
 #pragma unroll
   for (int c = 0; c < M; ++c) A[c] = A0[c];
-  u128 *Mo = has_parent ? msg_of(B, T.msg_slot, row) : nullptr;
-  u128 *Co = T.cut_side >= 0 ? msg_of(B, T.cmsg_slot, row) : nullptr;
+  N *Mo = has_parent ? Op::out(B, T.msg_slot, row) : nullptr;
+  N *Co = T.cut_side >= 0 ? Op::out(B, T.cmsg_slot, row) : nullptr;
   for (int p0 = s0; p0 < s1; p0 += kSweepU) {
     NodeRec rr[kSweepU];
 #pragma unroll
@@ -615,12 +681,12 @@ __device__ void node_sweeps(const NodeTask &T, const NodeRec *rec, int L,
       const int a = (int)(r.aj >> 16);
       const int j = (int)(r.aj & 0xFFFF);
       if (a < M) {
-        G += times_others<M>(mul_s64_u128(r.v, r.mu), A, a);
+        G += times_others<M>(Op::muls(r.v, Op::rec(r)), A, a);
 #pragma unroll
         for (int c = 0; c < M; ++c)
-          if (c == a) A[c] -= r.mu;
+          if (c == a) A[c] -= Op::rec(r);
       } else {
-        const u128 p = times_others<M>(s64_to_u128(r.v), A, a);
+        const N p = times_others<M>(Op::of(r.v), A, a);
         const bool is_parent = has_parent && a == M;
         (is_parent ? Mo : Co)[j] = p + G;
       }
@@ -630,7 +696,7 @@ __device__ void node_sweeps(const NodeTask &T, const NodeRec *rec, int L,
 
 __global__ __launch_bounds__(kNodeThreads) void node_kernel(
     const NodeTask *tasks, EstBuffers B) {
-  __shared__ u128 sh[kNodeThreads];
+  __shared__ u128 sh[kNodeThreads / 64];
   const NodeTask *Tg = tasks + blockIdx.x;
   const NodeTask T = *Tg;
   if (!T.guard.on) return;  // uniform
@@ -650,6 +716,17 @@ __global__ __launch_bounds__(kNodeThreads) void node_kernel(
   // the merged records come from node_merge_kernel
   if (T.mode == kModeTriRootPrep) return;  // apex_prep_kernel
 
+  if (T.guard.on & kOnDouble) {
+    double *shd = reinterpret_cast<double *>(sh);
+    switch (m) {
+      case 2: node_sweeps<2>(T, rec, L, row, B, shd); break;
+      case 3: node_sweeps<3>(T, rec, L, row, B, shd); break;
+      case 4: node_sweeps<4>(T, rec, L, row, B, shd); break;
+      case 5: node_sweeps<5>(T, rec, L, row, B, shd); break;
+      default: node_sweeps<kMaxChild>(T, rec, L, row, B, shd); break;
+    }
+    return;
+  }
   switch (m) {
     case 2: node_sweeps<2>(T, rec, L, row, B, sh); break;
     case 3: node_sweeps<3>(T, rec, L, row, B, sh); break;
@@ -672,33 +749,30 @@ __global__ __launch_bounds__(kNodeThreads) void node_kernel(
 // of mu and v * mu in that order, M(q) is one binary search and one read.
 // node1_prefix_kernel: chunk-local exclusive prefix sums (and chunk
 // totals); node1_emit_kernel: the messages (or, at a tree root, X).
-__device__ __forceinline__ u128 *n1_prefix(const EstBuffers &B, int slot,
-                                           int row) {
-  return reinterpret_cast<u128 *>(B.nrec +
-                                  ((size_t)slot * B.d + row) * (size_t)B.Lmax);
+template <class N>
+__device__ __forceinline__ N *n1_prefix(const EstBuffers &B, int slot,
+                                        int row) {
+  return reinterpret_cast<N *>(B.nrec +
+                               ((size_t)slot * B.d + row) * (size_t)B.Lmax);
 }
-__device__ __forceinline__ u128 *n1_total(const EstBuffers &B, int slot,
-                                          int row) {
-  return B.n1tot + ((size_t)slot * B.d + row) * (2 * kN1MaxChunks);
-}
-
-// 128-bit value of lane (lane - off), or 0 below lane off
-__device__ __forceinline__ u128 shfl_up_u128(u128 v, int off) {
-  const int lane = (int)threadIdx.x & 63;
-  u128 r = 0;
-#pragma unroll
-  for (int k = 3; k >= 0; --k)
-    r = (r << 32) | (uint32_t)__shfl_up((int)(uint32_t)(v >> (32 * k)), off);
-  return lane >= off ? r : (u128)0;
+template <class N>
+__device__ __forceinline__ N *n1_total(const EstBuffers &B, int slot,
+                                       int row) {
+  return reinterpret_cast<N *>(B.n1tot +
+                               ((size_t)slot * B.d + row) * (2 * kN1MaxChunks));
 }
 
-__global__ __launch_bounds__(kN1Threads) void node1_prefix_kernel(
-    const NodeTask *tasks, EstBuffers B, GridMap gm) {
-  const GridPos gp = grid_pos(gm);
-  if (!gp.ok) return;
-  __shared__ u128 sh_m[kN1Threads / 64], sh_x[kN1Threads / 64];
-  const NodeTask &T = tasks[gp.task];
-  if (T.m != 1 || !T.guard.on) return;
+// value of lane (lane - off), or 0 below lane off
+template <class N>
+__device__ __forceinline__ N shfl_up_or0(N v, int off) {
+  const N r = Num<N>::template shfl<false>(v, off);
+  return ((int)threadIdx.x & 63) >= off ? r : (N)0;
+}
+
+template <class N>
+__device__ __forceinline__ void node1_prefix(const NodeTask &T, const EstBuffers &B,
+                                             const GridPos &gp, N *sh_m, N *sh_x) {
+  using Op = Num<N>;
   const int row = gp.row;
   const int w = B.w;
   const int c0 = gp.c * kN1Chunk;
@@ -706,7 +780,7 @@ __global__ __launch_bounds__(kN1Threads) void node1_prefix_kernel(
   const int cside = T.child_side[0];
   const int cmsg = T.child_msg[0];
   const uint64_t *srt = sorted_of(B, cside, row);
-  u128 pm[kN1Per], px[kN1Per];
+  N pm[kN1Per], px[kN1Per];
   const int k0 = c0 + threadIdx.x * kN1Per;
 #pragma unroll
   for (int u = 0; u < kN1Per; ++u) {
@@ -714,12 +788,12 @@ __global__ __launch_bounds__(kN1Threads) void node1_prefix_kernel(
     const int k = k0 + u;
     if (k < w) {
       const int j = (int)(srt[k] & 0xFFFF);
-      const u128 mu = child_msg_at(B, cmsg, row, j);
+      const N mu = Op::child(B, cmsg, row, j);
       pm[u] = mu;
-      px[u] = mul_s64_u128(counter_at(B, cside, row, j), mu);
+      px[u] = Op::muls(counter_at(B, cside, row, j), mu);
     }
   }
-  u128 tm = 0, tx = 0;
+  N tm = 0, tx = 0;
 #pragma unroll
   for (int u = 0; u < kN1Per; ++u) {
     tm += pm[u];
@@ -727,11 +801,11 @@ __global__ __launch_bounds__(kN1Threads) void node1_prefix_kernel(
   }
   // inclusive block scans of the thread sums: within the waves by
   // shuffles, then the earlier waves' totals
-  u128 im = tm, ix = tx;
+  N im = tm, ix = tx;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
-    im += shfl_up_u128(im, off);
-    ix += shfl_up_u128(ix, off);
+    im += shfl_up_or0(im, off);
+    ix += shfl_up_or0(ix, off);
   }
   const int wave = (int)threadIdx.x >> 6;
   if (((int)threadIdx.x & 63) == 63) {
@@ -739,7 +813,7 @@ __global__ __launch_bounds__(kN1Threads) void node1_prefix_kernel(
     sh_x[wave] = ix;
   }
   __syncthreads();
-  u128 bm = 0, bx = 0;  // the earlier waves' totals, and the block's
+  N bm = 0, bx = 0;  // the earlier waves' totals, and the block's
 #pragma unroll
   for (int k = 0; k < kN1Threads / 64; ++k) {
     if (k < wave) {
@@ -747,8 +821,8 @@ __global__ __launch_bounds__(kN1Threads) void node1_prefix_kernel(
       bx += sh_x[k];
     }
   }
-  u128 em = bm + im - tm, ex = bx + ix - tx;
-  u128 *P = n1_prefix(B, T.scratch_slot, row);
+  N em = bm + im - tm, ex = bx + ix - tx;
+  N *P = n1_prefix<N>(B, T.scratch_slot, row);
   // a tree root (no parent or cut list) needs the chunk totals only
   const bool queries = T.parent_side >= 0 || T.cut_side >= 0;
 #pragma unroll
@@ -762,31 +836,42 @@ __global__ __launch_bounds__(kN1Threads) void node1_prefix_kernel(
     ex += px[u];
   }
   if (threadIdx.x == kN1Threads - 1) {
-    u128 *tot = n1_total(B, T.scratch_slot, row);
+    N *tot = n1_total<N>(B, T.scratch_slot, row);
     tot[2 * gp.c] = bm + im;
     tot[2 * gp.c + 1] = bx + ix;
   }
 }
 
-__global__ __launch_bounds__(kN1Threads) void node1_emit_kernel(
+__global__ __launch_bounds__(kN1Threads) void node1_prefix_kernel(
     const NodeTask *tasks, EstBuffers B, GridMap gm) {
   const GridPos gp = grid_pos(gm);
   if (!gp.ok) return;
-  extern __shared__ uint32_t smag[];  // the child's sorted |v| (int32 counters)
-  __shared__ u128 soff[2 * kN1MaxChunks + 2];
+  __shared__ u128 sh_m[kN1Threads / 64], sh_x[kN1Threads / 64];
   const NodeTask &T = tasks[gp.task];
-  if (T.m != 1 || !T.guard.on) return;
+  const int on = T.guard.on;
+  if (T.m != 1 || !on) return;
+  if (on & kOnDouble)
+    node1_prefix(T, B, gp, reinterpret_cast<double *>(sh_m), reinterpret_cast<double *>(sh_x));
+  else
+    node1_prefix(T, B, gp, sh_m, sh_x);
+}
+
+// smag: the child's sorted |v| (int32 counters); soff: chunk offsets
+template <class N>
+__device__ __forceinline__ void node1_emit(const NodeTask &T, const EstBuffers &B,
+                                           const GridPos &gp, uint32_t *smag, N *soff) {
+  using Op = Num<N>;
   const int row = gp.row;
   const int w = B.w;
   const int has_parent = T.parent_side >= 0;
   const int nq = has_parent + (T.cut_side >= 0);
   const int nch = (w + kN1Chunk - 1) / kN1Chunk;
-  const u128 *tot = n1_total(B, T.scratch_slot, row);
+  const N *tot = n1_total<N>(B, T.scratch_slot, row);
   if (nq == 0) {  // tree root: X = G(+inf)
     if (gp.c == 0 && threadIdx.x == 0) {
-      u128 x = 0;
+      N x = 0;
       for (int c = 0; c < nch; ++c) x += tot[2 * c + 1];
-      B.xout[(size_t)T.out_slot * B.d + row] = x;
+      *Op::root(B, T.out_slot, row) = x;
     }
     return;
   }
@@ -800,13 +885,13 @@ __global__ __launch_bounds__(kN1Threads) void node1_emit_kernel(
     // chunk offsets: lane c loads chunk c's totals, an exclusive scan over
     // the lanes (nch <= kN1MaxChunks <= 64)
     const int c = (int)threadIdx.x;
-    const u128 tm = c < nch ? tot[2 * c] : (u128)0;
-    const u128 tx = c < nch ? tot[2 * c + 1] : (u128)0;
-    u128 im = tm, ix = tx;
+    const N tm = c < nch ? tot[2 * c] : (N)0;
+    const N tx = c < nch ? tot[2 * c + 1] : (N)0;
+    N im = tm, ix = tx;
 #pragma unroll
     for (int off = 1; off < kN1MaxChunks; off <<= 1) {
-      im += shfl_up_u128(im, off);
-      ix += shfl_up_u128(ix, off);
+      im += shfl_up_or0(im, off);
+      ix += shfl_up_or0(ix, off);
     }
     if (c < nch) {
       soff[2 * c] = im - tm;
@@ -818,8 +903,8 @@ __global__ __launch_bounds__(kN1Threads) void node1_emit_kernel(
     }
   }
   __syncthreads();
-  const u128 *P = n1_prefix(B, T.scratch_slot, row);
-  const u128 tot_m = soff[2 * nch];
+  const N *P = n1_prefix<N>(B, T.scratch_slot, row);
+  const N tot_m = soff[2 * nch];
   int r[kN1Per], qi[kN1Per], qa[kN1Per];
   int64_t sv[kN1Per];
   uint64_t t[kN1Per];
@@ -859,7 +944,7 @@ __global__ __launch_bounds__(kN1Threads) void node1_emit_kernel(
 #pragma unroll
   for (int u = 0; u < kN1Per; ++u) {
     if (!ok[u]) continue;
-    u128 pm, px;
+    N pm, px;
     if (r[u] == w) {
       pm = tot_m;
       px = soff[2 * nch + 1];
@@ -869,9 +954,24 @@ __global__ __launch_bounds__(kN1Threads) void node1_emit_kernel(
       px = soff[2 * c + 1] + P[2 * (size_t)r[u] + 1];
     }
     const bool par = has_parent && qa[u] == 0;
-    u128 *out = msg_of(B, par ? T.msg_slot : T.cmsg_slot, row);
-    out[qi[u]] = mul_s64_u128(sv[u], tot_m - pm) + px;
+    N *out = Op::out(B, par ? T.msg_slot : T.cmsg_slot, row);
+    out[qi[u]] = Op::muls(sv[u], tot_m - pm) + px;
   }
+}
+
+__global__ __launch_bounds__(kN1Threads) void node1_emit_kernel(
+    const NodeTask *tasks, EstBuffers B, GridMap gm) {
+  const GridPos gp = grid_pos(gm);
+  if (!gp.ok) return;
+  extern __shared__ uint32_t smag[];
+  __shared__ u128 soff[2 * kN1MaxChunks + 2];
+  const NodeTask &T = tasks[gp.task];
+  const int on = T.guard.on;
+  if (T.m != 1 || !on) return;
+  if (on & kOnDouble)
+    node1_emit(T, B, gp, smag, reinterpret_cast<double *>(soff));
+  else
+    node1_emit(T, B, gp, smag, soff);
 }
 
 // min(a * b, 2^63) for a <= 2^63, b < 2^63
@@ -917,21 +1017,50 @@ __device__ int tri_path(ConstTask &T, const EstBuffers &B) {
 
 // Every task's guard (and a triangle's arithmetic path) resolved once per
 // estimate into guard.on, so that the later launches test one field of the
-// task they load anyway instead of re-reading the selected-row counts.
-// Index i: triangle tasks first, then node tasks.
-__device__ void resolve_task(const ResolveArgs &R, int i, const EstBuffers &B) {
+// task they load anyway instead of re-reading the selected-row counts.  A
+// workgroup of kSortThreads lanes takes one task a lane: triangle tasks
+// first, then node tasks.  Twins in double run where a tree sub-plan whose
+// 128-bit values are not certified holds their tables; the workgroup lists
+// those sub-plans first (lds: kSortThreads masks and a count).
+__device__ void resolve_block(const ResolveArgs &R, int block, const EstBuffers &B,
+                              uint64_t *lds) {
+  const int i = block * kSortThreads + (int)threadIdx.x;
+  bool twin = false;
+  NodeTask *N = nullptr;
   if (i < R.n_tri) {
     TriTask &T = R.tris[i];
     const bool on = COMPASS_GUARD_ON(T.guard, B.n_sel);
     T.guard.on = on ? 1 + tri_path(*(ConstTask *)&T, B) : 0;
   } else if (i < R.n_tri + R.n) {
-    NodeTask &T = R.tasks[i - R.n_tri];
-    int on = COMPASS_GUARD_ON(T.guard, B.n_sel) ? 1 : 0;
-    if (on && T.mode == kModeTriRootPrep && T.m == 2 &&
-        tri_path(*(ConstTask *)(R.tris + T.tri), B) == kTriFast)
-      on |= 2;
-    T.guard.on = on;
+    N = R.tasks + (i - R.n_tri);
+    twin = N->fp != 0;
+    if (!twin) {
+      int on = COMPASS_GUARD_ON(N->guard, B.n_sel) ? 1 : 0;
+      if (on && N->mode == kModeTriRootPrep && N->m == 2 &&
+          tri_path(*(ConstTask *)(R.tris + N->tri), B) == kTriFast)
+        on |= 2;
+      N->guard.on = on;
+    }
   }
+  if (!R.any_fp) return;
+  int *s_n = reinterpret_cast<int *>(lds + kSortThreads);
+  bool need = false;
+  for (int s0 = 0; s0 < R.n_sps; s0 += kSortThreads) {
+    __syncthreads();   // the last list is read
+    if (threadIdx.x == 0) *s_n = 0;
+    __syncthreads();
+    const int s = s0 + (int)threadIdx.x;
+    if (s < R.n_sps && R.sps[s].type == kSpTree &&
+        !subplan_certified(R.sps[s], B.n_sel, R.n_tables, B.w))
+      lds[atomicAdd(s_n, 1)] = R.sps[s].mask;
+    __syncthreads();
+    const int n = *s_n;
+    if (twin)
+      for (int k = 0; k < n && !need; ++k) need = (N->tables & ~lds[k]) == 0;
+  }
+  // a root belongs to one sub-plan (its tables are the sub-plan's mask), but
+  // a wider uncertified one may hold them too: then it runs unread
+  if (twin) N->guard.on = need ? 1 + kOnDouble : 0;
 }
 
 
@@ -1976,8 +2105,9 @@ __global__ __launch_bounds__(kLaneThreads) void tri_lane_kernel(
 // per sub-plan: rows, median, double, certificate
 // ---------------------------------------------------------------------
 __global__ void finish_kernel(const SubplanTask *sps, EstBuffers B,
-                              const double *approx, uint64_t *row_est,
-                              double *est, int32_t *flags, int32_t n_tables) {
+                              uint64_t *row_est, double *est, int32_t *flags,
+                              int32_t n_tables) {
+  const double *approx = B.approx;
   __shared__ u128 xs[64], ps[64];
   __shared__ double xd[64];
   const SubplanTask S = sps[blockIdx.x];
@@ -2113,6 +2243,7 @@ hipError_t launch_sort_rows(const SortJob *jobs, int n_jobs,
   // scan scratch and the waves' bases; rows of more than 8 keys a thread:
   // keys unpadded, the scratch and bases in the keys' space
   const bool pad = kpt <= 8;
+  // (more than the resolving workgroups' kSortThreads masks and a count)
   const size_t lds =
       (size_t)(kpt * kSortThreads + (pad ? kpt * kSortThreads / 16 : 0)) *
           sizeof(uint64_t) +
@@ -2203,10 +2334,10 @@ hipError_t launch_tri_lane(const TriTask *tasks, int n, const TriGroup *groups,
 }
 
 hipError_t launch_finish(const SubplanTask *sps, int n, const EstBuffers &B,
-                         const double *approx, uint64_t *row_est, double *est,
-                         int32_t *flags, int32_t n_tables, hipStream_t st) {
-  hipLaunchKernelGGL(finish_kernel, dim3(n), dim3(64), 0, st, sps, B, approx,
-                     row_est, est, flags, n_tables);
+                         uint64_t *row_est, double *est, int32_t *flags,
+                         int32_t n_tables, hipStream_t st) {
+  hipLaunchKernelGGL(finish_kernel, dim3(n), dim3(64), 0, st, sps, B, row_est,
+                     est, flags, n_tables);
   return hipGetLastError();
 }
 

@@ -12,7 +12,7 @@ constexpr int kMaxEstimateW = 16384;  // per-(sketch,row) sort held in LDS
 constexpr int kSortThreads = 1024;    // one workgroup sorts a row's keys
 constexpr int kSortKpt = kMaxEstimateW / kSortThreads;  // keys per thread
 constexpr int kNodeStageBytes = 96 * 1024;  // node merge: staged magnitudes
-constexpr size_t kNodeScratchBytes = (size_t)1 << 30;  // per level launch
+constexpr size_t kNodeScratchBytes = (size_t)2 << 30;  // per level launch
 constexpr int kMaxGridZ = 65535;  // tasks per launch (grid z)
 constexpr int kMergeThreads = 512;  // node list merge
 constexpr int kMergeChunk = 2048;  // merged elements per workgroup
@@ -43,8 +43,9 @@ enum { kModeMessage = 0, kModeTreeRoot = 1, kModeTriRootPrep = 2 };
 // candidate) does work.  n <= 1: always runs.  `on` is resolved on the
 // device once per estimate, before the other launches (resolve_kernel):
 // 0 = the task does nothing; a node task: 1, plus 2 for a two-child apex
-// whose sweep is the compact one; a triangle task: 1 + its arithmetic path
-// (kTriFast, kTriNarrow, kTriWide).
+// whose sweep is the compact one, plus kOnDouble for a twin in double; a
+// triangle task: 1 + its arithmetic path (kTriFast, kTriNarrow, kTriWide).
+constexpr int kOnDouble = 4;
 struct TaskGuard {
   int32_t n;
   int32_t self;
@@ -75,7 +76,13 @@ struct NodeTask {
   int32_t child_cut[kMaxChild];   // mode 2: index (0/1) of the cut endpoint, or -1
   int32_t child_parent_eid[kMaxChild];  // mode 2: edge id of the child's parent edge
   int32_t tri;                    // mode 2: its triangle task
-  int32_t pad;
+  // 1: the node's twin in double, for tree sub-plans whose 128-bit values
+  // are not certified.  Its message slots are those of the double messages
+  // (EstBuffers::fmsg), a root's out_slot one of EstBuffers::approx, and it
+  // runs only where such a sub-plan holds every table of `tables` (the
+  // node's subtree).
+  int32_t fp;
+  uint64_t tables;
 };
 
 // Triangle sub-plan: the root (apex) sweeps its merged child list once per
@@ -114,11 +121,15 @@ struct SortJob {
 
 // The tasks whose guards resolve_task sets (blocks: workgroups of
 // kSortThreads lanes for them, one task a lane).
+struct SubplanTask;
 struct ResolveArgs {
   NodeTask *tasks;
   TriTask *tris;
+  const SubplanTask *sps;
   int32_t n, n_tri;
-  int32_t blocks, pad;
+  int32_t n_sps, n_tables;
+  int32_t blocks;
+  int32_t any_fp;    // some task is a twin in double
 };
 
 struct SubplanTask {
