@@ -30,6 +30,7 @@
 namespace compass {
 // kernels (build_kernels.hip, estimate_kernels.hip)
 hipError_t launch_fill_zero(void *p, int64_t bytes, hipStream_t st);
+hipError_t launch_fetch_pinned(const void *src, void *dst, int64_t bytes, hipStream_t st);
 hipError_t launch_fill_zero_list(const ZeroSpans &z, hipStream_t st);
 hipError_t launch_scan_sketch(const BuildParams &P, int n_blocks,
                               size_t lds_bytes, hipStream_t st);
@@ -182,6 +183,10 @@ static compass_status ensure_scratch(DeviceState *ds, hipStream_t stream,
   return COMPASS_OK;
 }
 
+// Tables above this go through the copy engine: reads over the bus by one
+// launch are faster for the few KB to few hundred KB of a usual call.
+constexpr size_t kFetchMax = (size_t)1 << 20;
+
 // copies `bytes` of host data to `dst` (device) asynchronously through a
 // pinned staging buffer that is reused only once its copy has completed
 static compass_status upload(DeviceState *ds, void *dst, const void *src,
@@ -193,12 +198,17 @@ static compass_status upload(DeviceState *ds, void *dst, const void *src,
   if (ds->pinned_bytes[k] < bytes) {
     if (ds->pinned[k]) HIP_OK(hipHostFree(ds->pinned[k]));
     ds->pinned[k] = nullptr;
-    size_t want = std::max(bytes, (size_t)65536);
+    const size_t want = (std::max(bytes, (size_t)65536) + 255) & ~(size_t)255;
     HIP_OK(hipHostMalloc(&ds->pinned[k], want, hipHostMallocDefault));
     ds->pinned_bytes[k] = want;
   }
   memcpy(ds->pinned[k], src, bytes);
-  HIP_OK(hipMemcpyAsync(dst, ds->pinned[k], bytes, hipMemcpyHostToDevice, st));
+  // whole 16-byte words: the staging buffer and what the callers reserve at
+  // `dst` are multiples of 256 bytes
+  if (bytes <= kFetchMax)
+    HIP_OK(launch_fetch_pinned(ds->pinned[k], dst, (int64_t)bytes, st));
+  else
+    HIP_OK(hipMemcpyAsync(dst, ds->pinned[k], bytes, hipMemcpyHostToDevice, st));
   HIP_OK(hipEventRecord(ds->pinned_done[k], st));
   ds->pinned_used[k] = true;
   return COMPASS_OK;

@@ -410,6 +410,7 @@ struct CounterList {
   void *p[kMaxSketches];
 };
 
+template <bool kCounted>
 __global__ void slab_reduce_kernel(const int32_t *__restrict__ slab,
                                    int64_t chunks, int32_t n_slices, int32_t d,
                                    int32_t w, CounterList cl,
@@ -435,7 +436,7 @@ __global__ void slab_reduce_kernel(const int32_t *__restrict__ slab,
       const int gs = (int)(k / w);
       const int j = (int)(k - (int64_t)gs * w);
       const int s = gs / d, row = gs - s * d;
-      if (cmap.st) chunks = cmap.counted(s) ? cmap.slice_chunks[gs] : scan_chunks;
+      if (kCounted) chunks = cmap.counted(s) ? cmap.slice_chunks[gs] : scan_chunks;
       int64_t a[4] = {0, 0, 0, 0};
       int64_t c = 0;
       for (; c + 8 <= chunks; c += 8) {
@@ -484,7 +485,7 @@ __global__ void slab_reduce_kernel(const int32_t *__restrict__ slab,
     const int gs = (int)(k / w);
     const int j = (int)(k - (int64_t)gs * w);
     const int s = gs / d, row = gs - s * d;
-    if (cmap.st) chunks = cmap.counted(s) ? cmap.slice_chunks[gs] : scan_chunks;
+    if (kCounted) chunks = cmap.counted(s) ? cmap.slice_chunks[gs] : scan_chunks;
     // eight chunk rows in flight per lane
     int64_t a8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     int64_t c = 0;
@@ -538,9 +539,14 @@ hipError_t launch_slab_reduce(const int32_t *slab, int64_t chunks,
   int64_t blocks = (total / (vec4 ? 4 : 1) + 255) / 256;
   if (blocks > 1024) blocks = 1024;
   if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(slab_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0,
-                     st, slab, chunks, n_slices, d, w, cl, counter_bits,
-                     accumulate, fc, cmap, vec4);
+  if (cmap.st)
+    hipLaunchKernelGGL(slab_reduce_kernel<true>, dim3((unsigned)blocks), dim3(256), 0,
+                       st, slab, chunks, n_slices, d, w, cl, counter_bits,
+                       accumulate, fc, cmap, vec4);
+  else
+    hipLaunchKernelGGL(slab_reduce_kernel<false>, dim3((unsigned)blocks), dim3(256), 0,
+                       st, slab, chunks, n_slices, d, w, cl, counter_bits,
+                       accumulate, fc, cmap, vec4);
   return hipGetLastError();
 }
 
@@ -564,6 +570,25 @@ hipError_t launch_store_seeds(const RowSeeds *src, int n, RowSeeds *dst,
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+// A call's tables from pinned host memory to device memory, 16 bytes a lane.
+// (The runtime's asynchronous copy of a few tens of KB leaves the stream
+// idle for 27 us on either side of the engine's work, two blit copies 30 us;
+// this launch and its reads over the bus take 5.)
+__global__ void fetch_pinned_kernel(const uint4 *__restrict__ src, uint4 *__restrict__ dst,
+                                    int64_t n) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    dst[i] = src[i];
+}
+
+hipError_t launch_fetch_pinned(const void *src, void *dst, int64_t bytes, hipStream_t st) {
+  const int64_t n = (bytes + 15) / 16;
+  const int64_t blocks = std::min<int64_t>((n + 255) / 256, 256);
+  hipLaunchKernelGGL(fetch_pinned_kernel, dim3((unsigned)blocks), dim3(256), 0, st,
+                     reinterpret_cast<const uint4 *>(src), reinterpret_cast<uint4 *>(dst), n);
+  return hipGetLastError();
 }
 
 // zero-fill used instead of hipMemsetAsync so that callers may capture the
