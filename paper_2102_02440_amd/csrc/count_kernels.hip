@@ -68,9 +68,11 @@ __device__ __forceinline__ uint32_t block_exclusive_sum(uint32_t v, uint32_t *s_
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;   // a key of more than 32 bits
 constexpr uint16_t kNoRec = kCntBinKeys;   // padding: counted past the bin
 
-// The tile's raw keys of one lane (rows tid + k * 1024), streamed.  Buffer
-// loads: one lane offset for every row (the row step is the scalar offset);
-// a load past the tile's end returns 0.
+// The tile's raw keys of one lane (rows tid + k * 1024), streamed.  A whole
+// tile by buffer loads: one lane offset for every row, the row step in the
+// scalar offset.  The last tile's by plain loads at clamped rows: the range
+// check of a buffer load compares with the buffer's size less the scalar
+// offset, which a short buffer does not hold.
 typedef int int2v __attribute__((ext_vector_type(2)));
 template <class T>
 struct RawKeys;
@@ -78,13 +80,21 @@ template <>
 struct RawKeys<int32_t> {
   int v[kCntKeys];
   __device__ __forceinline__ void load(const CountCol &c, int64_t base, int nt) {
-    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<int32_t *>(reinterpret_cast<const int32_t *>(c.col) + base), 0,
-        nt * 4, 0x00027000);
+    const int32_t *col = reinterpret_cast<const int32_t *>(c.col) + base;
+    if (nt == kCntTile) {
+      const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(col), 0,
+                                                          kCntTile * 4, 0x00027000);
 #pragma unroll
-    for (int k = 0; k < kCntKeys; ++k)
-      v[k] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)threadIdx.x * 4,
-                                                  k * kCntThreads * 4, 2);
+      for (int k = 0; k < kCntKeys; ++k)
+        v[k] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)threadIdx.x * 4,
+                                                    k * kCntThreads * 4, 2);
+    } else {
+#pragma unroll
+      for (int k = 0; k < kCntKeys; ++k) {
+        v[k] = col[min((int)threadIdx.x + k * kCntThreads, nt - 1)];
+        if (k % 4 == 3) __asm__ volatile("" ::: "memory");  // few addresses at once
+      }
+    }
   }
   __device__ __forceinline__ uint32_t key(int k) const { return (uint32_t)v[k]; }
 };
@@ -92,13 +102,22 @@ template <>
 struct RawKeys<int64_t> {
   int2v v[kCntKeys];
   __device__ __forceinline__ void load(const CountCol &c, int64_t base, int nt) {
-    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<int64_t *>(reinterpret_cast<const int64_t *>(c.col) + base), 0,
-        nt * 8, 0x00027000);
+    const int64_t *col = reinterpret_cast<const int64_t *>(c.col) + base;
+    if (nt == kCntTile) {
+      const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int64_t *>(col), 0,
+                                                          kCntTile * 8, 0x00027000);
 #pragma unroll
-    for (int k = 0; k < kCntKeys; ++k)
-      v[k] = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)threadIdx.x * 8,
-                                                  k * kCntThreads * 8, 2);
+      for (int k = 0; k < kCntKeys; ++k)
+        v[k] = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)threadIdx.x * 8,
+                                                    k * kCntThreads * 8, 2);
+    } else {
+#pragma unroll
+      for (int k = 0; k < kCntKeys; ++k) {
+        v[k] = *reinterpret_cast<const int2v *>(
+            col + min((int)threadIdx.x + k * kCntThreads, nt - 1));
+        if (k % 4 == 3) __asm__ volatile("" ::: "memory");
+      }
+    }
   }
   __device__ __forceinline__ uint32_t key(int k) const {
     return v[k].y ? kNoKey : (uint32_t)v[k].x;
