@@ -7,19 +7,28 @@
 // (master, Adam state) and in bfloat16 (the copy the products read); every
 // layer rounds its input activations to bfloat16 and accumulates in fp32.
 //
-// Kernels (tiny dense layers: H <= 64, so plain FP32 FMA over LDS tiles; a
-// matrix-core tile would sit idle at these shapes):
-//   mlp_fwd_kernel     8 samples per workgroup (64 workgroups per 512-sample
-//                      batch); layer weights staged in LDS;
-//                      saves rounded inputs and pre-activations for training
-//   mlp_bwd_kernel     per-workgroup partial gradients (deterministic slab)
+// Kernels: a workgroup takes 16 samples, a wave 16 of a layer's outputs, the
+// products on the matrix cores in fp32 (v_mfma_f32_16x16x4_f32: each result
+// is the chain of fused multiply-adds over the inputs in ascending order,
+// the same bits as a scalar loop; measured on random, cancelling and tiny
+// values).  A step is 0.04 GFLOP, so its latency counts: the weights are
+// kept a second time as float images in the order of the fragments, both
+// ways round, and go from memory to registers in one round of loads.
+// 512-sample steps of the 20-64-64-64-1 network: 64 us with staged weight
+// tiles and scalar products, 18 us so (step 14, sum and Adam 4).  Every sum keeps one order
+// (inputs ascending, samples ascending within groups of 8, groups
+// ascending), in fp32.
+//   mlp_fwd_kernel     forward pass, tiles walked by a persistent grid
+//   mlp_step_kernel    forward and backward, partial gradients of every
+//                      8 samples (deterministic slab)
 //   mlp_reduce_adam_kernel  sums the slab in a fixed order, then Adam on
-//                      the fp32 masters and the bfloat16 copy
+//                      the fp32 masters and the weight images
 //   mlp_features_kernel  sub-plan features from the 128-bit row estimates
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
 
+#include <algorithm>
 #include <cmath>
 #include <string>
 #include <vector>
@@ -31,8 +40,18 @@ namespace compass {
 
 constexpr int kMlpMaxDim = 64;
 constexpr int kMlpMaxLayers = 8;
-constexpr int kMlpTile = 8;        // samples per workgroup
-constexpr int kMlpThreads = 256;
+constexpr int kMlpPart = 8;        // samples of one gradient partial
+constexpr int kMlpTile = 16;       // samples per workgroup
+constexpr int kMlpThreads = 256;   // a wave per 16 outputs
+
+// Images of a layer's weights, rounded to bfloat16: row o holds input i at
+// mlp_slot(i) (and the other way round: row i holds output o), 64 x 64 with
+// zeros where the layer is narrower; then its biases (fp32, 64).
+constexpr int kMlpImage = kMlpMaxDim * kMlpMaxDim;
+__device__ __host__ constexpr int mlp_slot(int i) { return (i & 3) * 16 + (i >> 2); }
+// rows of activations and deltas in LDS (words): 16-byte aligned, 4 words off
+// a multiple of the banks
+constexpr int kMlpRow = kMlpMaxDim + 4;
 
 struct MlpShape {
   int32_t n_layers;                  // weight layers (hidden + output)
@@ -57,155 +76,314 @@ __device__ __forceinline__ float round_bf16(float f) {
   return bf16_to_f(f_to_bf16(f));
 }
 
-// Forward pass of up to kMlpTile samples.  act: [layer][sample][kMlpMaxDim]
-// rounded layer inputs, pre: [layer][sample][kMlpMaxDim] pre-activations
-// (both only when `save`).  Sample s reads row idx[s] of x and base (row s
-// when idx is null).
-__global__ __launch_bounds__(kMlpThreads) void mlp_fwd_kernel(
-    MlpShape S, const uint16_t *__restrict__ wb, const float *__restrict__ p,
-    const float *__restrict__ x, const float *__restrict__ base,
-    const int32_t *__restrict__ idx, int32_t n, float *__restrict__ y,
-    float *__restrict__ act, float *__restrict__ pre, int32_t save) {
-  __shared__ float a[kMlpTile][kMlpMaxDim + 1];
-  __shared__ float z[kMlpTile][kMlpMaxDim + 1];
-  __shared__ float W[kMlpMaxDim][kMlpMaxDim + 1];
-  __shared__ float bb[kMlpMaxDim];
-  const int s0 = blockIdx.x * kMlpTile;
-  const int n_in = S.dim[0];
-  for (int k = threadIdx.x; k < kMlpTile * n_in; k += kMlpThreads) {
-    const int s = k / n_in, i = k % n_in;
-    if (s0 + s < n) {
-      const size_t r = idx ? (size_t)idx[s0 + s] : (size_t)(s0 + s);
-      a[s][i] = round_bf16(x[r * n_in + i]);
-    } else {
-      a[s][i] = 0.f;
-    }
-  }
-  for (int l = 0; l < S.n_layers; ++l) {
-    const int di = S.dim[l], dout = S.dim[l + 1];
-    for (int k = threadIdx.x; k < dout * di; k += kMlpThreads)
-      W[k / di][k % di] = bf16_to_f(wb[S.woff[l] + k]);
-    for (int k = threadIdx.x; k < dout; k += kMlpThreads) bb[k] = p[S.boff[l] + k];
-    __syncthreads();
-    if (save) {
-      for (int k = threadIdx.x; k < kMlpTile * di; k += kMlpThreads) {
-        const int s = k / di, i = k % di;
-        if (s0 + s < n)
-          act[((size_t)l * n + s0 + s) * kMlpMaxDim + i] = a[s][i];
-      }
-    }
-    for (int k = threadIdx.x; k < kMlpTile * dout; k += kMlpThreads) {
-      const int s = k / dout, o = k % dout;
-      float acc = 0.f;
-      for (int i = 0; i < di; ++i) acc = fmaf(a[s][i], W[o][i], acc);
-      z[s][o] = acc + bb[o];
-    }
-    __syncthreads();
-    const bool last = (l == S.n_layers - 1);
-    for (int k = threadIdx.x; k < kMlpTile * dout; k += kMlpThreads) {
-      const int s = k / dout, o = k % dout;
-      const float v = z[s][o];
-      if (save && s0 + s < n) pre[((size_t)l * n + s0 + s) * kMlpMaxDim + o] = v;
-      if (!last) a[s][o] = round_bf16(v > 0.f ? v : 0.f);
-    }
-    __syncthreads();
-  }
-  for (int s = threadIdx.x; s < kMlpTile; s += kMlpThreads)
-    if (s0 + s < n) y[s0 + s] = base[idx ? idx[s0 + s] : s0 + s] + z[s][0];
+__device__ __forceinline__ float lane_value(float v, int i) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
 }
 
-// Backward pass: dL/dy = 2 (y - t) / n; partial gradients of this
-// workgroup's samples go to slab[blockIdx.x][param]; loss partial too.
-// Sample s's target is t[idx[s]] (t[s] when idx is null).
-__global__ __launch_bounds__(kMlpThreads) void mlp_bwd_kernel(
-    MlpShape S, const uint16_t *__restrict__ wb, const float *__restrict__ y,
-    const float *__restrict__ t, const int32_t *__restrict__ idx, int32_t n,
-    const float *__restrict__ act,
-    const float *__restrict__ pre, float *__restrict__ slab,
-    float *__restrict__ loss_part) {
-  __shared__ float dz[kMlpTile][kMlpMaxDim + 1];
-  __shared__ float da[kMlpTile][kMlpMaxDim + 1];
-  __shared__ float ar[kMlpTile][kMlpMaxDim + 1];
-  __shared__ float W[kMlpMaxDim][kMlpMaxDim + 1];
-  __shared__ float red[kMlpThreads];
-  const int s0 = blockIdx.x * kMlpTile;
-  float* part = slab + (size_t)blockIdx.x * S.n_params;
-  float lsum = 0.f;
-  for (int s = threadIdx.x; s < kMlpTile; s += kMlpThreads) {
-    float g = 0.f;
-    if (s0 + s < n) {
-      const float r = y[s0 + s] - t[idx ? idx[s0 + s] : s0 + s];
-      g = 2.f * r / (float)n;
-      lsum += r * r;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// 16 words of one lane in chunks of four, as many as `k` inputs need: lane
+// (n = lane & 15, q = lane >> 4) of a fragment holds inputs 4 s + q at word s.
+struct Frag {
+  f32x4 v[4];
+  __device__ __forceinline__ void load(const float *row, int k) {
+    const int q = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      v[c] = f32x4{0, 0, 0, 0};
+      if (16 * c < k) v[c] = *reinterpret_cast<const f32x4 *>(row + 16 * q + 4 * c);
     }
-    dz[s][0] = g;
   }
-  red[threadIdx.x] = lsum;
-  __syncthreads();
-  for (int off = kMlpThreads / 2; off > 0; off >>= 1) {
-    if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-    __syncthreads();
+};
+
+// D = A B, the inputs in ascending order: A's rows the samples (row = lane &
+// 15), B's columns the outputs; lane (n, q) gets samples 4 q + r of column n.
+__device__ __forceinline__ f32x4 mlp_product(const Frag &a, const Frag &b, int k) {
+  f32x4 acc = {0, 0, 0, 0};
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    if (16 * c >= k) break;   // uniform
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[c][u], b.v[c][u], acc, 0, 0, 0);
   }
-  if (threadIdx.x == 0) loss_part[blockIdx.x] = red[0];
-  for (int l = S.n_layers - 1; l >= 0; --l) {
-    const int di = S.dim[l], dout = S.dim[l + 1];
-    for (int k = threadIdx.x; k < kMlpTile * di; k += kMlpThreads) {
-      const int s = k / di, i = k % di;
-      ar[s][i] = (s0 + s < n) ? act[((size_t)l * n + s0 + s) * kMlpMaxDim + i] : 0.f;
+  return acc;
+}
+
+// The weights of a wave's 16 columns of every layer and their biases.
+struct MlpWeights {
+  Frag w[kMlpMaxLayers];
+  float bias[kMlpMaxLayers];
+  __device__ __forceinline__ void load(const MlpShape &S, const float *__restrict__ img) {
+    const int col = 16 * (threadIdx.x >> 6) + (threadIdx.x & 15);
+#pragma unroll
+    for (int l = 0; l < kMlpMaxLayers; ++l) {
+      if (l >= S.n_layers) break;
+      w[l].load(img + (size_t)l * kMlpImage + col * kMlpMaxDim,
+                16 * (threadIdx.x >> 6) < S.dim[l + 1] ? S.dim[l] : 0);
+      bias[l] = img[(size_t)2 * S.n_layers * kMlpImage + l * kMlpMaxDim + col];
     }
-    for (int k = threadIdx.x; k < dout * di; k += kMlpThreads)
-      W[k / di][k % di] = bf16_to_f(wb[S.woff[l] + k]);
+  }
+};
+
+// Rounded inputs of the tile's samples (row idx[s] of x, row s when idx is
+// null; zeros past the last) to LDS.  All lanes call it.
+__device__ __forceinline__ void mlp_load_inputs(const float *__restrict__ x,
+                                                const int32_t *__restrict__ idx, int s0, int n,
+                                                int n_in, float *a) {
+  // a wave takes four samples, a lane one input
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  float v[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int s = min(s0 + 4 * wave + u, n - 1);
+    const size_t r = idx ? (size_t)idx[s] : (size_t)s;
+    v[u] = x[r * n_in + min(lane, n_in - 1)];
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const bool in = s0 + 4 * wave + u < n && lane < n_in;
+    a[(4 * wave + u) * kMlpRow + mlp_slot(lane)] = in ? round_bf16(v[u]) : 0.f;
+  }
+}
+
+__global__ __launch_bounds__(kMlpThreads) void mlp_fwd_kernel(
+    MlpShape S, const float *__restrict__ img, const float *__restrict__ x,
+    const float *__restrict__ base, int32_t n, float *__restrict__ y) {
+  __shared__ __align__(16) float s_a[2][kMlpTile * kMlpRow];
+  MlpWeights W;
+  W.load(S, img);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int m = lane & 15, q = lane >> 4, col = 16 * wave + m;
+  const int tiles = (n + kMlpTile - 1) / kMlpTile;
+  for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
+    const int s0 = t * kMlpTile;
+    mlp_load_inputs(x, nullptr, s0, n, S.dim[0], s_a[0]);
     __syncthreads();
-    // dW[o][i] = sum_s dz[s][o] ar[s][i]; db[o] = sum_s dz[s][o]
-    for (int k = threadIdx.x; k < dout * di; k += kMlpThreads) {
-      const int o = k / di, i = k % di;
-      float acc = 0.f;
-      for (int s = 0; s < kMlpTile; ++s) acc = fmaf(dz[s][o], ar[s][i], acc);
-      part[S.woff[l] + k] = acc;
-    }
-    for (int o = threadIdx.x; o < dout; o += kMlpThreads) {
-      float acc = 0.f;
-      for (int s = 0; s < kMlpTile; ++s) acc += dz[s][o];
-      part[S.boff[l] + o] = acc;
-    }
-    if (l > 0) {
-      // da[s][i] = sum_o dz[s][o] W[o][i]; dz_prev = da * (pre_prev > 0)
-      for (int k = threadIdx.x; k < kMlpTile * di; k += kMlpThreads) {
-        const int s = k / di, i = k % di;
-        float acc = 0.f;
-        for (int o = 0; o < dout; ++o) acc = fmaf(dz[s][o], W[o][i], acc);
-        const float zp =
-            (s0 + s < n) ? pre[((size_t)(l - 1) * n + s0 + s) * kMlpMaxDim + i] : 0.f;
-        da[s][i] = zp > 0.f ? acc : 0.f;
+#pragma unroll
+    for (int l = 0; l < kMlpMaxLayers; ++l) {
+      if (l >= S.n_layers) break;
+      const int di = S.dim[l], dout = S.dim[l + 1];
+      float *next = s_a[(l + 1) & 1];
+      if (16 * wave < dout) {
+        Frag a;
+        a.load(s_a[l & 1] + m * kMlpRow, di);
+        const f32x4 z = mlp_product(a, W.w[l], di);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float v = z[r] + W.bias[l];
+          if (l == S.n_layers - 1) {
+            const int s = s0 + 4 * q + r;
+            if (col == 0 && s < n) y[s] = base[s] + v;
+          } else {
+            next[(4 * q + r) * kMlpRow + mlp_slot(col)] = round_bf16(v > 0.f ? v : 0.f);
+          }
+        }
       }
       __syncthreads();
-      for (int k = threadIdx.x; k < kMlpTile * di; k += kMlpThreads) {
-        const int s = k / di, i = k % di;
-        dz[s][i] = da[s][i];
+    }
+  }
+}
+
+// Forward and backward of the workgroup's samples (sample s reads row idx[s]
+// of x, base and t, row s when idx is null): dL/dy = 2 (y - t) / n; the
+// gradient partials of its two groups of 8 samples go to slab[group][param],
+// the loss partials too.  Layer inputs and deltas of all layers stay in LDS
+// for the weight gradients, pre-activations in registers.
+__global__ __launch_bounds__(kMlpThreads) void mlp_step_kernel(
+    MlpShape S, const float *__restrict__ img, const float *__restrict__ x,
+    const float *__restrict__ base, const float *__restrict__ t,
+    const int32_t *__restrict__ idx, int32_t n, int32_t parts, float *__restrict__ slab,
+    float *__restrict__ loss_part) {
+  extern __shared__ __align__(16) float lds[];   // [layer][sample][kMlpRow] twice
+  __shared__ float s_r2[kMlpTile];
+  constexpr int kLayer = kMlpTile * kMlpRow;
+  float *ars = lds, *dzs = lds + S.n_layers * kLayer;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int m = lane & 15, q = lane >> 4, col = 16 * wave + m;
+  const int s0 = blockIdx.x * kMlpTile;
+  // the samples whose results a lane gets, for the last layer
+  size_t row[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int s = min(s0 + 4 * q + r, n - 1);
+    row[r] = idx ? (size_t)idx[s] : (size_t)s;
+  }
+  MlpWeights W;
+  W.load(S, img);
+  Frag wt[kMlpMaxLayers];
+#pragma unroll
+  for (int l = 1; l < kMlpMaxLayers; ++l) {
+    if (l >= S.n_layers) break;
+    wt[l].load(img + (size_t)(S.n_layers + l) * kMlpImage + col * kMlpMaxDim,
+               16 * wave < S.dim[l] ? S.dim[l + 1] : 0);
+  }
+  float y0[4], target[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    y0[r] = base[row[r]];
+    target[r] = t[row[r]];
+  }
+  mlp_load_inputs(x, idx, s0, n, S.dim[0], ars);
+  __syncthreads();
+
+  f32x4 z[kMlpMaxLayers];
+#pragma unroll
+  for (int l = 0; l < kMlpMaxLayers; ++l) {
+    if (l >= S.n_layers) break;
+    const int di = S.dim[l], dout = S.dim[l + 1];
+    const bool last = l == S.n_layers - 1;
+    z[l] = f32x4{0, 0, 0, 0};
+    if (16 * wave < dout) {
+      Frag a;
+      a.load(ars + l * kLayer + m * kMlpRow, di);
+      z[l] = mlp_product(a, W.w[l], di);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const bool valid = s0 + 4 * q + r < n;
+        const float v = z[l][r] + W.bias[l];
+        z[l][r] = valid ? v : 0.f;
+        if (last) {
+          const float res = valid ? y0[r] + v - target[r] : 0.f;
+          const float g = valid ? 2.f * res / (float)n : 0.f;
+          // (zeros in the other columns: the products take 16 outputs)
+          dzs[l * kLayer + (4 * q + r) * kMlpRow + mlp_slot(col)] = col ? 0.f : g;
+          if (col == 0) s_r2[4 * q + r] = res * res;
+        } else {
+          ars[(l + 1) * kLayer + (4 * q + r) * kMlpRow + mlp_slot(col)] =
+              valid ? round_bf16(v > 0.f ? v : 0.f) : 0.f;
+        }
       }
     }
     __syncthreads();
   }
+  if (threadIdx.x < 2 && 2 * blockIdx.x + threadIdx.x < parts) {
+    const float *r2 = s_r2 + kMlpPart * threadIdx.x;
+    loss_part[2 * blockIdx.x + threadIdx.x] =
+        ((r2[0] + r2[4]) + (r2[2] + r2[6])) + ((r2[1] + r2[5]) + (r2[3] + r2[7]));
+  }
+  // deltas of the layers below: through the weights, where the
+  // pre-activation was positive
+#pragma unroll
+  for (int l = kMlpMaxLayers - 1; l > 0; --l) {
+    if (l >= S.n_layers) continue;
+    const int di = S.dim[l], dout = S.dim[l + 1];
+    if (16 * wave < di) {
+      Frag a;
+      a.load(dzs + l * kLayer + m * kMlpRow, dout);
+      const f32x4 d = mlp_product(a, wt[l], dout);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        dzs[(l - 1) * kLayer + (4 * q + r) * kMlpRow + mlp_slot(col)] =
+            z[l - 1][r] > 0.f ? d[r] : 0.f;
+    }
+    __syncthreads();
+  }
+  // dW[o][i] = sum_s dz[s][o] a[s][i]: a wave takes 16 rows o, every 16
+  // columns i, the two groups of 8 samples apart; db[o] = sum_s dz[s][o].
+  // Buffer stores: a lane offset past the end (rows and columns the layer
+  // does not have, a group past the last) writes nothing, with no branch.
+  // (The scalar offset, 64 c, is below the parameters' bytes wherever it is
+  // used: a layer then has more than 16 c inputs.)
+  const bool two = 2 * (int)blockIdx.x + 1 < parts;
+  float *part0 = slab + (size_t)2 * blockIdx.x * S.n_params;
+  __amdgpu_buffer_rsrc_t part[2];
+#pragma unroll
+  for (int g = 0; g < 2; ++g)
+    part[g] = __builtin_amdgcn_make_buffer_rsrc(part0 + (size_t)g * S.n_params, 0,
+                                                S.n_params * 4, 0x00027000);
+  constexpr int kPast = 0x7FFFFFFF;
+#pragma unroll
+  for (int l = 0; l < kMlpMaxLayers; ++l) {
+    if (l >= S.n_layers) break;
+    const int di = S.dim[l], dout = S.dim[l + 1];
+    if (16 * wave >= dout) continue;
+    // sample 4 u + q, u = 0, 1: the first group; 2, 3: the second
+    const float *dz = dzs + l * kLayer + q * kMlpRow + mlp_slot(col);
+    const float *ar = ars + l * kLayer + q * kMlpRow + mlp_slot(m);
+    float da[4], av[4][4], dbs[kMlpPart];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      da[u] = dz[4 * u * kMlpRow];
+      // mlp_slot(16 c + m) = mlp_slot(m) + 4 c
+#pragma unroll
+      for (int c = 0; c < 4; ++c) av[c][u] = ar[4 * u * kMlpRow + 4 * c];
+    }
+    // the bias of column `col`: lanes q = 0, 1 take a group each
+#pragma unroll
+    for (int k = 0; k < kMlpPart; ++k)
+      dbs[k] = dzs[l * kLayer + (kMlpPart * (q & 1) + k) * kMlpRow + mlp_slot(col)];
+    int off[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int o = 16 * wave + 4 * q + r;
+      off[r] = o < dout ? (S.woff[l] + o * di + m) * 4 : kPast;
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (16 * c >= di) break;
+      const bool in = 16 * c + m < di;
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        f32x4 d = {0, 0, 0, 0};
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(da[2 * g], av[c][2 * g], d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(da[2 * g + 1], av[c][2 * g + 1], d, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(d[r]), part[g],
+                                                in && (g == 0 || two) ? off[r] : kPast,
+                                                64 * c, 0);
+      }
+    }
+    float db = 0.f;
+#pragma unroll
+    for (int k = 0; k < kMlpPart; ++k) db += dbs[k];
+    const int boff = col < dout ? (S.boff[l] + col) * 4 : kPast;
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(db), part[0], q == 0 ? boff : kPast, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(db), part[1],
+                                          q == 1 && two ? boff : kPast, 0, 0);
+  }
 }
 
-// Gradient = sum of the workgroups' partials (in workgroup order, eight
+// Gradient = sum of the workgroups' partials (in workgroup order, 32
 // partials' loads in flight per lane), then, when `adam`, the Adam update
-// of the same parameter (fp32 master, moments, bfloat16 copy).  Lane 0 of
-// workgroup 0 also sums the loss partials.
-__global__ void mlp_reduce_adam_kernel(
+// of the same parameter (fp32 master, moments, weight images: places `at`,
+// the second one -1 for biases).  The last workgroup sums the loss partials.
+constexpr int kAdamThreads = 64;
+
+// a parameter's places in the images: weights rounded to bfloat16, both ways
+// round; biases as they are
+__device__ __forceinline__ void mlp_to_images(float p, int2 at, float *__restrict__ img) {
+  if (at.y >= 0) {
+    const float w = round_bf16(p);
+    img[at.x] = w;
+    img[at.y] = w;
+  } else {
+    img[at.x] = p;
+  }
+}
+
+__global__ __launch_bounds__(kAdamThreads) void mlp_reduce_adam_kernel(
     const float *__restrict__ slab, int32_t parts, int32_t n_params,
     float *__restrict__ g, const float *__restrict__ loss_part,
     float *__restrict__ loss, float inv_n, int32_t adam, float *__restrict__ p,
-    float *__restrict__ m, float *__restrict__ v, uint16_t *__restrict__ wb,
-    float lr, float b1, float b2, float eps, float c1, float c2) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k == 0 && loss) {
+    float *__restrict__ m, float *__restrict__ v, float *__restrict__ img,
+    const int2 *__restrict__ at, float lr, float b1, float b2, float eps, float c1, float c2) {
+  if (blockIdx.x == gridDim.x - 1) {
+    if (!loss) return;
     float acc = 0.f;
-    for (int b = 0; b < parts; ++b) acc += loss_part[b];
-    *loss = acc * inv_n;  // mean squared error
+    for (int b0 = 0; b0 < parts; b0 += kAdamThreads) {
+      const int b = b0 + (int)threadIdx.x;
+      const float q = b < parts ? loss_part[b] : 0.f;
+      for (int u = 0; u < min(kAdamThreads, parts - b0); ++u) acc += lane_value(q, u);
+    }
+    if (threadIdx.x == 0) *loss = acc * inv_n;  // mean squared error
+    return;
   }
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n_params) return;
-  constexpr int kU = 8;
+  constexpr int kU = 32;
   float acc = 0.f;
   for (int b0 = 0; b0 < parts; b0 += kU) {
     float t[kU];
@@ -224,13 +402,13 @@ __global__ void mlp_reduce_adam_kernel(
   v[k] = vk;
   const float pk = p[k] - lr * (mk / c1) / (sqrtf(vk / c2) + eps);
   p[k] = pk;
-  wb[k] = f_to_bf16(pk);
+  mlp_to_images(pk, at[k], img);
 }
 
-__global__ void mlp_to_bf16_kernel(const float *__restrict__ p,
-                                   uint16_t *__restrict__ wb, int32_t n) {
+__global__ void mlp_images_kernel(const float *__restrict__ p, const int2 *__restrict__ at,
+                                  float *__restrict__ img, int32_t n) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n) wb[k] = f_to_bf16(p[k]);
+  if (k < n) mlp_to_images(p[k], at[k], img);
 }
 
 // The query's join graph in kernel arguments (edge endpoints).
@@ -360,9 +538,9 @@ static compass_status mfail(compass_status s, const std::string &m) {
 struct compass_mlp_s {
   MlpShape S;
   float *p = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
-  uint16_t *wb = nullptr;
-  float *act = nullptr, *pre = nullptr, *slab = nullptr, *loss_part = nullptr;
-  float *y = nullptr;
+  float *img = nullptr;   // weight images (kMlpImage)
+  int2 *at = nullptr;     // every parameter's places in them
+  float *slab = nullptr, *loss_part = nullptr;
   int32_t cap = 0;     // samples the training buffers hold
   int64_t step = 0;
 };
@@ -391,6 +569,7 @@ extern "C" compass_status compass_mlp_create(int32_t n_in, int32_t hidden,
   }
   S.n_params = off;
   const size_t b = sizeof(float) * off;
+  const size_t img_words = (size_t)S.n_layers * (2 * kMlpImage + kMlpMaxDim);
   auto bad = [&](hipError_t e) {
     if (e != hipSuccess) {
       delete M;
@@ -400,14 +579,28 @@ extern "C" compass_status compass_mlp_create(int32_t n_in, int32_t hidden,
   };
   if (bad(hipMalloc(&M->p, b)) || bad(hipMalloc(&M->m, b)) ||
       bad(hipMalloc(&M->v, b)) || bad(hipMalloc(&M->g, b)) ||
-      bad(hipMalloc(&M->wb, sizeof(uint16_t) * off)))
+      bad(hipMalloc(&M->img, sizeof(float) * img_words)) ||
+      bad(hipMalloc(&M->at, sizeof(int2) * off)))
     return mfail(COMPASS_E_HIP, "hipMalloc failed");
+  std::vector<int2> at(off);
+  for (int l = 0; l < S.n_layers; ++l) {
+    const int di = S.dim[l], dout = S.dim[l + 1];
+    for (int o = 0; o < dout; ++o) {
+      for (int i = 0; i < di; ++i)
+        at[S.woff[l] + o * di + i] =
+            make_int2(l * kMlpImage + o * kMlpMaxDim + mlp_slot(i),
+                      (S.n_layers + l) * kMlpImage + i * kMlpMaxDim + mlp_slot(o));
+      at[S.boff[l] + o] = make_int2(2 * S.n_layers * kMlpImage + l * kMlpMaxDim + o, -1);
+    }
+  }
+  MHIP(hipMemcpy(M->at, at.data(), sizeof(int2) * off, hipMemcpyHostToDevice));
+  MHIP(hipMemset(M->img, 0, sizeof(float) * img_words));
   MHIP(hipMemcpy(M->p, init, b, hipMemcpyHostToDevice));
   MHIP(hipMemset(M->m, 0, b));
   MHIP(hipMemset(M->v, 0, b));
   MHIP(hipMemset(M->g, 0, b));
-  hipLaunchKernelGGL(mlp_to_bf16_kernel, dim3((off + 255) / 256), dim3(256), 0,
-                     0, M->p, M->wb, off);
+  hipLaunchKernelGGL(mlp_images_kernel, dim3((off + 255) / 256), dim3(256), 0,
+                     0, M->p, M->at, M->img, off);
   MHIP(hipGetLastError());
   MHIP(hipDeviceSynchronize());
   *out = M;
@@ -428,50 +621,44 @@ extern "C" compass_status compass_mlp_forward(compass_mlp M, const float *x,
   if (!M || (n > 0 && (!x || !base || !y)) || n < 0)
     return mfail(COMPASS_E_ARG, "bad argument");
   if (n == 0) return COMPASS_OK;
-  hipLaunchKernelGGL(mlp_fwd_kernel, dim3((n + kMlpTile - 1) / kMlpTile),
-                     dim3(kMlpThreads), 0, st, M->S, M->wb, M->p, x, base,
-                     (const int32_t *)nullptr, n, y, nullptr, nullptr, 0);
+  const int64_t tiles = ((int64_t)n + kMlpTile - 1) / kMlpTile;
+  hipLaunchKernelGGL(mlp_fwd_kernel, dim3((unsigned)std::min<int64_t>(tiles, 1024)),
+                     dim3(kMlpThreads), 0, st, M->S, M->img, x, base, n, y);
   MHIP(hipGetLastError());
   return COMPASS_OK;
 }
 
 // One Adam step on samples idx[0..n) of (x, base, target) (rows 0..n when
-// idx is null); grows the activation buffers when n exceeds them.
+// idx is null); grows the gradient slab when n exceeds it.
 static compass_status train_batch(compass_mlp M, const float *x,
                                   const float *base, const float *target,
                                   const int32_t *idx, int32_t n, float lr,
                                   float *loss, hipStream_t st) {
-  const int blocks = (n + kMlpTile - 1) / kMlpTile;
+  const int parts = (n + kMlpPart - 1) / kMlpPart;
   if (n > M->cap) {
     (void)hipDeviceSynchronize();
-    (void)hipFree(M->act);
-    (void)hipFree(M->pre);
     (void)hipFree(M->slab);
     (void)hipFree(M->loss_part);
-    (void)hipFree(M->y);
-    M->act = M->pre = M->slab = M->loss_part = M->y = nullptr;
-    const size_t per = (size_t)M->S.n_layers * n * kMlpMaxDim * sizeof(float);
-    MHIP(hipMalloc(&M->act, per));
-    MHIP(hipMalloc(&M->pre, per));
-    MHIP(hipMalloc(&M->slab, (size_t)blocks * M->S.n_params * sizeof(float)));
-    MHIP(hipMalloc(&M->loss_part, (size_t)blocks * sizeof(float)));
-    MHIP(hipMalloc(&M->y, (size_t)n * sizeof(float)));
+    M->slab = M->loss_part = nullptr;
+    M->cap = 0;
+    MHIP(hipMalloc(&M->slab, (size_t)parts * M->S.n_params * sizeof(float)));
+    MHIP(hipMalloc(&M->loss_part, (size_t)parts * sizeof(float)));
     M->cap = n;
   }
-  hipLaunchKernelGGL(mlp_fwd_kernel, dim3(blocks), dim3(kMlpThreads), 0, st,
-                     M->S, M->wb, M->p, x, base, idx, n, M->y, M->act, M->pre, 1);
-  hipLaunchKernelGGL(mlp_bwd_kernel, dim3(blocks), dim3(kMlpThreads), 0, st,
-                     M->S, M->wb, M->y, target, idx, n, M->act, M->pre, M->slab,
-                     M->loss_part);
+  const size_t lds = 2 * (size_t)M->S.n_layers * kMlpTile * kMlpRow * sizeof(float);
+  hipLaunchKernelGGL(mlp_step_kernel, dim3((n + kMlpTile - 1) / kMlpTile),
+                     dim3(kMlpThreads), lds, st, M->S, M->img, x, base, target, idx, n,
+                     parts, M->slab, M->loss_part);
   const int np = M->S.n_params;
   if (lr > 0.f) M->step += 1;  // a gradient-only call is not an Adam step
   const float b1 = 0.9f, b2 = 0.999f;
   const float c1 = 1.f - powf(b1, (float)M->step);
   const float c2 = 1.f - powf(b2, (float)M->step);
-  hipLaunchKernelGGL(mlp_reduce_adam_kernel, dim3((np + 255) / 256), dim3(256),
-                     0, st, M->slab, blocks, np, M->g, M->loss_part, loss,
-                     1.f / (float)n, lr > 0.f ? 1 : 0, M->p, M->m, M->v, M->wb,
-                     lr, b1, b2, 1e-8f, c1, c2);
+  hipLaunchKernelGGL(mlp_reduce_adam_kernel,
+                     dim3((np + kAdamThreads - 1) / kAdamThreads + 1), dim3(kAdamThreads),
+                     0, st, M->slab, parts, np, M->g, M->loss_part, loss,
+                     1.f / (float)n, lr > 0.f ? 1 : 0, M->p, M->m, M->v, M->img,
+                     M->at, lr, b1, b2, 1e-8f, c1, c2);
   MHIP(hipGetLastError());
   return COMPASS_OK;
 }
@@ -524,8 +711,8 @@ extern "C" compass_status compass_mlp_write(compass_mlp M, const float *params,
   if (adam_m) MHIP(hipMemcpy(M->m, adam_m, b, hipMemcpyHostToDevice));
   if (adam_v) MHIP(hipMemcpy(M->v, adam_v, b, hipMemcpyHostToDevice));
   M->step = step;
-  hipLaunchKernelGGL(mlp_to_bf16_kernel, dim3((M->S.n_params + 255) / 256),
-                     dim3(256), 0, 0, M->p, M->wb, M->S.n_params);
+  hipLaunchKernelGGL(mlp_images_kernel, dim3((M->S.n_params + 255) / 256),
+                     dim3(256), 0, 0, M->p, M->at, M->img, M->S.n_params);
   MHIP(hipGetLastError());
   MHIP(hipDeviceSynchronize());
   return COMPASS_OK;
@@ -538,12 +725,10 @@ extern "C" compass_status compass_mlp_destroy(compass_mlp M) {
   (void)hipFree(M->m);
   (void)hipFree(M->v);
   (void)hipFree(M->g);
-  (void)hipFree(M->wb);
-  (void)hipFree(M->act);
-  (void)hipFree(M->pre);
+  (void)hipFree(M->img);
+  (void)hipFree(M->at);
   (void)hipFree(M->slab);
   (void)hipFree(M->loss_part);
-  (void)hipFree(M->y);
   delete M;
   return COMPASS_OK;
 }
