@@ -88,7 +88,8 @@ hipError_t launch_scan2d_binned(const BuildParams &P, const Bin2dArgs &a,
                                 int accumulate, hipStream_t st);
 hipError_t launch_chain3(const ChainArgs &a, uint64_t *row_est, double *est,
                          int32_t *flags, hipStream_t st);
-hipError_t launch_agms_build(const AgmsParams &P, int n_blocks, hipStream_t st);
+hipError_t launch_agms_build(const AgmsParams &P, int n_blocks, int n_cu,
+                             hipStream_t st);
 hipError_t launch_agms_estimate(const AgmsEstArgs &a, uint64_t *row_sums,
                                 double *est, int32_t *flag, hipStream_t st);
 }  // namespace compass
@@ -2281,6 +2282,18 @@ extern "C" compass_status compass_estimate_partitioned(
 // ---------------------------------------------------------------------
 // AGMS baseline (Section 4.1)
 // ---------------------------------------------------------------------
+// Sign tables: from this many sign evaluations of a scan without predicates
+// on, as far as the signs and the gathers take four fifths of the direct
+// scan's time at most (per row and join 1.4 ps per sketch evaluated there;
+// 1 / 1.88 ps per lane of the signs, 11 ps per gather that misses the L2), up
+// to this much scratch.  K = 112, one join, keys repeated 50 times: 37 us
+// direct and 40 by the tables at 1e7 evaluations, 98 and 43 at 5e7, 167 and 46
+// at 1e8, 310 and 52 at 2e8; a table whose keys do not repeat pays 10 to 20 us
+// of launches, which is up to 13 % at 1e8 and 6 % at 2e8.
+constexpr double kAgmsMinEvals = 2.0e8;
+constexpr double kAgmsLanesPerEval = 2.0, kAgmsLanesPerGather = 20;
+constexpr size_t kAgmsScratchCap = (size_t)1 << 30;
+
 extern "C" compass_status compass_agms_build(
     int64_t n_rows, const void *const *pred_cols, int32_t n_pred_cols,
     const compass_pred *preds, int32_t n_preds,
@@ -2343,10 +2356,48 @@ extern "C" compass_status compass_agms_build(
   if (st != COMPASS_OK) return st;
   void *scr;
   const size_t bytes = sizeof(RowSeeds) * sd.size();
-  st = ensure_scratch(ds, stream, bytes, &scr);
+  // sign tables: distinct columns, the keys each may hold, their scratch
+  AgmsTables &T = P.tab;
+  size_t total = align256(bytes);
+  const size_t o_state = total;
+  size_t o_signs[kAgmsMaxJoins];
+  if (n_preds == 0 && (double)n_rows * K * n_joins >= kAgmsMinEvals &&
+      kAgmsLanesPerEval * K > kAgmsLanesPerGather) {
+    T.n_groups = (K + kAgmsGroup - 1) / kAgmsGroup;
+    for (int e = 0; e < n_joins; ++e) {
+      int c = 0;
+      while (c < T.n_cols && !(T.col[c].col == P.keys[e].col &&
+                               T.col[c].dtype == P.keys[e].dtype))
+        ++c;
+      if (c == T.n_cols) T.col[T.n_cols++] = P.keys[e];
+      T.join[c][T.col_joins[c]++] = e;
+    }
+    T.most_lanes =
+        (int64_t)((double)n_rows * (kAgmsLanesPerEval * n_joins * K - kAgmsLanesPerGather * T.n_cols));
+    const size_t key_bytes = (size_t)T.n_cols * T.n_groups * sizeof(uint4);
+    total += 256;
+    for (int c = 0; c < T.n_cols; ++c) {
+      T.cap[c] = (uint32_t)std::min<int64_t>({kAgmsMaxRange, T.most_lanes / T.col_joins[c] / 64,
+                                              (int64_t)(kAgmsScratchCap / key_bytes)});
+      o_signs[c] = total;
+      total += align256((size_t)T.cap[c] * T.n_groups * sizeof(uint4));
+    }
+  }
+  st = ensure_scratch(ds, stream, total, &scr);
+  if (st != COMPASS_OK && T.n_cols > 0) {   // no room for the sign tables
+    (void)hipGetLastError();
+    g_err.clear();
+    memset(&T, 0, sizeof T);
+    st = ensure_scratch(ds, stream, align256(bytes), &scr);
+  }
   if (st != COMPASS_OK) return st;
   st = upload(ds, scr, sd.data(), bytes, stream);
   if (st != COMPASS_OK) return st;
+  if (T.n_cols > 0) {
+    char *c8 = reinterpret_cast<char *>(scr);
+    T.st = reinterpret_cast<AgmsState *>(c8 + o_state);
+    for (int c = 0; c < T.n_cols; ++c) T.signs[c] = reinterpret_cast<uint4 *>(c8 + o_signs[c]);
+  }
   P.seeds = reinterpret_cast<const RowSeeds *>(scr);
   if (!accumulate) {
     ProfScope ps("fill_zero", stream);
@@ -2354,12 +2405,25 @@ extern "C" compass_status compass_agms_build(
     HIP_OK(launch_fill_zero(n_selected, 8, stream));
   }
   if (n_rows == 0) return COMPASS_OK;
-  const int64_t tiles = (n_rows + kBuildTile - 1) / kBuildTile;
+  // A workgroup of 16 waves fills a CU, and a tile's evaluations are a chain
+  // in every lane: tables of few tiles take smaller ones, down to 32
+  // evaluations per lane, up to one workgroup per CU, or four where a lane
+  // keeps 64 (89,285 rows of one join, K = 112: 162 -> 37 us; 9,765 rows,
+  // K = 1024: 1340 -> 43 us; with four at 32, 625,000 rows, K = 16: 39 -> 43)
+  P.tile = kBuildTile;
+  const int parts = kBuildThreads / K;
+  for (;;) {
+    const int64_t half = P.tile / 2, per_lane = half / parts * n_joins;
+    const int64_t n_half = (n_rows + half - 1) / half;
+    if (per_lane < 32 || n_half > (per_lane < 64 ? 1 : 4) * (int64_t)ds->n_cu) break;
+    P.tile = (int32_t)half;
+  }
+  const int64_t tiles = (n_rows + P.tile - 1) / P.tile;
   const int64_t blocks = std::min<int64_t>(tiles, 4ll * ds->n_cu);
-  P.rows_per_chunk = (tiles + blocks - 1) / blocks * kBuildTile;
+  P.rows_per_chunk = (tiles + blocks - 1) / blocks * P.tile;
   const int64_t chunks = (n_rows + P.rows_per_chunk - 1) / P.rows_per_chunk;
   ProfScope ps("agms_build", stream);
-  HIP_OK(launch_agms_build(P, (int)chunks, stream));
+  HIP_OK(launch_agms_build(P, (int)chunks, ds->n_cu, stream));
   return COMPASS_OK;
 }
 

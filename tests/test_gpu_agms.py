@@ -137,3 +137,44 @@ def test_agms_full_size_cast_info_sampled(oracle):
         one = oracle.agms_sketch([tb.cols[col] for (_, _, col) in inc],
                                  [seeds[e][c:c + 1] for (e, _, _) in inc], 1, 1)
         assert got[c] == one[0, 0], c
+
+
+@gpu
+@pytest.mark.parametrize("n,r,b,joins,kind", [
+    (50_000, 16, 64, 4, "repeat"),       # 8 groups of 128 sketches
+    (3_100_001, 1, 33, 2, "repeat"),     # a ragged group, many rounds
+    (800_003, 10, 13, 2, "shared"),      # both joins on one column
+    (400_000, 4, 65, 2, "outside"),      # a few keys no table holds
+    (400_000, 4, 65, 2, "distinct"),     # nearly every key distinct
+])
+def test_agms_large_tables_without_predicates(oracle, n, r, b, joins, kind):
+    """Tables above the sign tables' threshold: counters bit for bit, twice
+    (the second call adds to the first)."""
+    torch = _torch()
+    from paper_2102_02440_amd import compass as C
+    rng = np.random.default_rng(n + joins)
+    if kind == "distinct":
+        keys = [rng.integers(-2**62, 2**62, n, dtype=np.int64) for _ in range(joins)]
+    else:
+        keys = [rng.integers(0, 1 + n // 50, n).astype(np.int64 if e % 2 else np.int32)
+                for e in range(joins)]
+    if kind == "outside":
+        at = rng.integers(0, n, 500)
+        keys[1][at] = rng.integers(-2**62, 2**62, 500, dtype=np.int64)
+        keys[0][at[:50]] = -7
+    seeds = W.draw_seeds(rng, joins, r * b)
+    _say("agms large", n, r, b, joins, kind)
+    dk = [torch.from_numpy(k).to("cuda") for k in keys]
+    if kind == "shared":
+        keys, dk = [keys[0]] * joins, [dk[0]] * joins
+    cnt = torch.zeros((r, b), dtype=torch.int64, device="cuda")
+    nsel = torch.zeros(1, dtype=torch.int64, device="cuda")
+    co = oracle.agms_sketch(keys, list(seeds), r, b)
+    C.agms_build(n, [], [], dk, list(seeds), cnt, nsel, r, b)
+    torch.cuda.synchronize()
+    assert np.array_equal(cnt.cpu().numpy(), co)
+    assert nsel.item() == n
+    C.agms_build(n, [], [], dk, list(seeds), cnt, nsel, r, b, accumulate=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(cnt.cpu().numpy(), 2 * co)
+    assert nsel.item() == 2 * n
