@@ -495,9 +495,11 @@ static bool plan_counted(const BuildParams &base, int n_sketches, int d,
   }
   int8_t counted[kMaxSketches];
   CountArgs &A = cp.a;
+  bool any = false;
+  for (int c = 0; c < n_all; ++c) any |= counted_bins(n_rows, users[c] * d) > 0;
   for (int c = 0; c < n_all; ++c) {
     counted[c] = -1;
-    const int bins = counted_bins(n_rows, users[c] * d);
+    const int bins = any ? counted_bins(n_rows, users[c] * d, true) : 0;
     if (bins < 1) continue;
     CountCol &col = A.c[A.n_cols];
     col.col = base.keys[first_of[c]].col;

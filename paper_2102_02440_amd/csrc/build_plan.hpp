@@ -120,12 +120,16 @@ constexpr int kCntMaxSg = 64;
 // updates per row: 3.3 ns per 1000 rows of a column against 1.6 ns per 1000
 // updates is 2.1, taken with a margin for clustered keys and narrow tables.
 // Below kCntMinUpdates the seven launches eat the gain: 63M updates of 4.5M
-// rows take 108 us counted and 146 us hashed row by row.
+// rows take 108 us counted and 146 us hashed row by row.  Where another
+// column of the table pays for them, kCntAlsoUpdates is enough
+// (7 sketch rows of 4.5M keys beside 14 of another column: 145 us hashed row
+// by row, 35 counted).
 constexpr double kCntRowCost = 3.5;
 constexpr double kCntMinUpdates = 5.0e7;   // below: launches would not pay
-inline int counted_bins(int64_t n_rows, int slices) {
+constexpr double kCntAlsoUpdates = 1.5e7;
+inline int counted_bins(int64_t n_rows, int slices, bool also = false) {
   if (n_rows >= ((int64_t)1 << 31) - kCntTile) return 0;  // int32 weights
-  if ((double)n_rows * slices < kCntMinUpdates) return 0;
+  if ((double)n_rows * slices < (also ? kCntAlsoUpdates : kCntMinUpdates)) return 0;
   const double share = 0.9 - kCntRowCost / slices;
   if (share <= 0) return 0;
   const double bins = (double)n_rows * share / kCntBinKeys;

@@ -125,3 +125,25 @@ def test_counted_mixed_columns(order, bits, accumulate):
     assert ns == nr == (n + 5 if accumulate else n)
     for g, r in zip(got, ref):
         assert np.array_equal(g, r)
+
+
+@gpu
+@pytest.mark.parametrize("order", ["zipf,zipf,sorted", "runs,few_outside,runs"])
+def test_counted_second_column(order):
+    """A column below the floor is counted along with one above it: equal to
+    hashing every row."""
+    torch = _torch()
+    from paper_2102_02440_amd import compass as C
+    names = order.split(",")
+    rng = np.random.default_rng(len(order))
+    d, w = 7, 4096
+    cols = {k: torch.from_numpy(_column(k, rng, N).astype(np.int32)).cuda()
+            for k in dict.fromkeys(names)}
+    keys = [cols[k] for k in names]
+    seeds = [W.draw_seeds(rng, 1, d)[0] for _ in names]
+    print("[case] counted second", order, "n", N, "d", d, "w", w, flush=True)
+    got, ns = _build(C, torch, N, keys, seeds, d, w, 32)
+    ref, nr = _build(C, torch, N, keys, seeds, d, w, 32, noalloc=True)
+    assert ns == nr == N
+    for g, r in zip(got, ref):
+        assert np.array_equal(g, r)
