@@ -83,6 +83,9 @@ hipError_t launch_tensor_finish(const u128 *partial, int n_chunks, int d,
                                 const int64_t *n_sel, int n_tables,
                                 uint64_t *row_est, double *est, int32_t *flags,
                                 hipStream_t st);
+hipError_t launch_scan2d_segments(const BuildParams &P, const SegArgs &a,
+                                  const KdDims &kx, int accumulate, int n_cu,
+                                  hipStream_t st);
 hipError_t launch_scan2d_binned(const BuildParams &P, const Bin2dArgs &a,
                                 const KdDims &kx,
                                 int accumulate, hipStream_t st);
@@ -1894,6 +1897,77 @@ static int bin2d_shift(int d, int w1, int w2) {
   return rs;
 }
 
+// The segmented build, in the same batches.  Up to kSegMaxBins tiles per
+// sketch row a chunk of 8192 rows has 32 records or more of each, a 64-byte
+// piece.  From kSegMinRows rows on: a chunk is twice the binned build's tile,
+// so few rows leave it fewer workgroups.  d = 5, 1024 x 1024 counters: 39 us
+// binned and 60 segmented at 100,000 rows, 75 and 71 at 1M, 511 and 280 at
+// 10M (55 and 68, 231 and 109 with a tenth of the rows selected); 2048 x 2048
+// (kSegMaxBins tiles): 90 and 89 at 1M, 834 and 271 at 10M.
+constexpr int64_t kSegMinRows = (int64_t)1 << 21;
+static compass_status sketch_build_2d_segments(const BuildParams &P,
+                                               const KdDims &kx,
+                                               DeviceState *ds, int64_t n_rows,
+                                               int64_t batch, int d, int w1,
+                                               int w2, int r_shift,
+                                               int accumulate,
+                                               hipStream_t stream) {
+  SegArgs a;
+  memset(&a, 0, sizeof(a));
+  a.d = d;
+  a.w1 = w1;
+  a.w2 = w2;
+  a.r_shift = r_shift;
+  a.nbr = (w1 + (1 << r_shift) - 1) >> r_shift;
+  a.n_bins = d * a.nbr;
+  // every part of a tile but its last holds 1 / (4 n_cu) of the records
+  a.max_items = (a.n_bins + 4 * ds->n_cu + 7) / 8 * 8;
+  const int64_t rows_max = std::min<int64_t>(n_rows, batch);
+  const int64_t tiles_max = (rows_max + kBuildTile - 1) / kBuildTile;
+  const int64_t blocks_max = std::min<int64_t>(tiles_max, ds->n_cu);
+  const int64_t rpb_max = (tiles_max + blocks_max - 1) / blocks_max * kBuildTile;
+  const int64_t chunks_max = blocks_max * ((rpb_max + kSegChunk - 1) / kSegChunk);
+  size_t total = 0;
+  auto carve = [&](size_t bytes) {
+    const size_t o = total;
+    total += align256(bytes);
+    return o;
+  };
+  const size_t o_tot = carve((size_t)(a.n_bins + 1) * 4);
+  const size_t o_items = carve(sizeof(SegItem) * a.max_items);
+  const size_t o_off = carve((size_t)chunks_max * d * (a.nbr + 1) * 2);
+  const size_t o_rec = carve(((size_t)chunks_max * d * kSegChunk + kSegPad) * 2);
+  void *scr;
+  compass_status st = ensure_scratch(ds, stream, total, &scr);
+  if (st != COMPASS_OK) return st;
+  char *c = reinterpret_cast<char *>(scr);
+  a.bin_total = reinterpret_cast<int32_t *>(c + o_tot);
+  a.n_items = a.bin_total + a.n_bins;
+  a.items = reinterpret_cast<SegItem *>(c + o_items);
+  a.off = reinterpret_cast<uint16_t *>(c + o_off);
+  a.rec = reinterpret_cast<uint16_t *>(c + o_rec);
+  if (!accumulate) {
+    ProfScope ps("fill_zero", stream);
+    HIP_OK(launch_fill_zero(P.n_selected, 8, stream));
+  }
+  for (int64_t b0 = 0; b0 < n_rows; b0 += batch) {
+    const int64_t b1 = std::min(n_rows, b0 + batch);
+    const int64_t tiles = (b1 - b0 + kBuildTile - 1) / kBuildTile;
+    const int64_t blocks = std::min<int64_t>(tiles, ds->n_cu);
+    a.rows_per_block = (tiles + blocks - 1) / blocks * kBuildTile;
+    a.n_blocks = (int32_t)((b1 - b0 + a.rows_per_block - 1) / a.rows_per_block);
+    a.block_chunks = (int32_t)((a.rows_per_block + kSegChunk - 1) / kSegChunk);
+    a.row0 = b0;
+    a.row1 = b1;
+    ProfScope ps("scan2d", stream);
+    HIP_OK(launch_fill_zero(a.bin_total, (int64_t)align256((size_t)(a.n_bins + 1) * 4),
+                            stream));
+    HIP_OK(launch_scan2d_segments(P, a, kx, (accumulate || b0 > 0) ? 1 : 0, ds->n_cu,
+                                  stream));
+  }
+  return COMPASS_OK;
+}
+
 // The binned build in batches of rows whose records (4 bytes per selected
 // row and sketch row) fit the record budget (1 GiB, or
 // COMPASS_2D_RECORD_BYTES); every batch after the first adds to the
@@ -1910,13 +1984,18 @@ static compass_status sketch_build_2d_binned(const BuildParams &P,
   }
   const int64_t batch = std::max<int64_t>(
       kBuildTile, budget / (4 * (int64_t)d) / kBuildTile * kBuildTile);
+  const int nbr = (w1 + (1 << r_shift) - 1) >> r_shift;
+  if (nbr <= kSegMaxBins && d * nbr <= kSegMaxTotal &&
+      std::min(n_rows, batch) >= kSegMinRows)
+    return sketch_build_2d_segments(P, kx, ds, n_rows, batch, d, w1, w2, r_shift,
+                                    accumulate, stream);
   Bin2dArgs a;
   memset(&a, 0, sizeof(a));
   a.d = d;
   a.w1 = w1;
   a.w2 = w2;
   a.r_shift = r_shift;
-  a.nbr = (w1 + (1 << r_shift) - 1) >> r_shift;
+  a.nbr = nbr;
   a.n_bins = d * a.nbr;
   // blocks of the scan: two per CU when their LDS (histogram + row queue)
   // allows it

@@ -430,6 +430,400 @@ hipError_t launch_scan2d_binned(const BuildParams &P, const Bin2dArgs &a,
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------
+// Segmented build: the binned build above for at most kSegMaxBins tiles per
+// sketch row, where a chunk of some thousand rows has whole cache lines of
+// records for every tile.  The records are grouped in LDS as they are made
+// and written once, in 16 bits, instead of written, read, scattered and read.
+//   seg_scan_kernel   predicate scan, survivors queued to chunks of 8192
+//                     rows; per chunk and sketch row the keys are hashed,
+//                     every record takes a rank of its tile by an LDS
+//                     atomic, and the grouped records and the tiles' starts
+//                     go to the chunk's region.  Bound by the hash: 36M rows
+//                     of three joins and five rows, 540M updates, take
+//                     950 us, 870 at the rate of a bare hash (binned: 1060,
+//                     and 1447 us to scatter).  512 lanes with chunks of 4096
+//                     rows take 905, but the shorter segments cost
+//                     seg_tile_kernel more than that.
+//   seg_plan_kernel   tiles with many records (frequent keys) split into
+//                     parts; the parts' tiles zeroed
+//   seg_tile_kernel   per tile and part: LDS sums of the segments, written
+//                     once (one part) or added.  230 us for 180M records of
+//                     640 tiles (binned: 375)
+// ---------------------------------------------------------------------
+// A lane's rows of a chunk: rows threadIdx.x + k * kBuildThreads of its n.
+struct SegRows {
+  const int32_t *queue;   // nullptr: consecutive rows
+  int64_t base;
+  int n;
+  template <int R>
+  __device__ __forceinline__ void load(const KeyDev &key, int h, uint64_t (&x)[R]) const {
+    int ridx[R];
+    int lane = threadIdx.x;
+    __asm__ volatile("" : "+v"(lane));   // per call: no addresses kept live
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const int q = min(lane + (h + k) * kBuildThreads, n - 1);
+      ridx[k] = queue ? queue[q] : q;
+    }
+    load_fields<R>(key, base, ridx, x);
+  }
+};
+
+// Signs and buckets of rows H .. H + 3 of a lane under one join's functions.
+// Keys below 2^32 wait in registers (x); others are loaded again.
+template <int H, int R>
+__device__ __forceinline__ void hash_four(const SegRows &rows, const KeyDev &key,
+                                          const uint32_t (&x)[R], const RowSeeds &s,
+                                          const BucketMod &bm, bool wide, bool pow2,
+                                          int32_t (&g)[4], uint32_t (&b)[4]) {
+  uint64_t xx[4];
+  if (wide) {
+    rows.load(key, H, xx);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) hash_xi_h<false>(xx[k], s, bm, g[k], b[k]);
+    return;
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) xx[k] = x[H + k];
+  if (pow2) {
+    hash_many_pow2_auto<4>(xx, s, bm.mask, g, b);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) hash_xi_h<true>(xx[k], s, bm, g[k], b[k]);
+  }
+}
+
+template <int H, int KD, int R>
+__device__ __forceinline__ void seg_records(const BuildParams &P, const SegArgs &a,
+                                            const KdDims &kx, const SegRows &rows, int i,
+                                            bool wide, bool pow2,
+                                            const uint32_t (&x)[4][R], uint32_t (&rec)[R]) {
+  const int d = a.d;
+  int32_t g1[4], g[4];
+  uint32_t b1[4], b2[4], b[4];
+  hash_four<H>(rows, P.keys[0], x[0], P.seeds[i], P.bm1, wide, pow2, g1, b1);
+  hash_four<H>(rows, P.keys[1], x[1], P.seeds[d + i], P.bm, wide, pow2, g, b2);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) g1[k] *= g[k];
+  if (KD > 2) {
+    hash_four<H>(rows, P.keys[2], x[2], P.seeds[2 * d + i], kx.bm3, wide, pow2, g, b);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      b2[k] = b2[k] * kx.bm3.w + b[k];
+      g1[k] *= g[k];
+    }
+  }
+  if (KD > 3) {
+    hash_four<H>(rows, P.keys[3], x[3], P.seeds[3 * d + i], kx.bm4, wide, pow2, g, b);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      b2[k] = b2[k] * kx.bm4.w + b[k];
+      g1[k] *= g[k];
+    }
+  }
+  const uint32_t rmask = (1u << a.r_shift) - 1;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t off = (b1[k] & rmask) * (uint32_t)a.w2 + b2[k];
+    rec[H + k] = (b1[k] >> a.r_shift) << 16 | off << 1 | (g1[k] < 0 ? 1u : 0u);
+  }
+}
+
+template <int KD>
+__global__ __launch_bounds__(kBuildThreads) void seg_scan_kernel(
+    const BuildParams P, const SegArgs a, const KdDims kx) {
+  constexpr int kChunk = kSegChunk;
+  constexpr int R = kChunk / kBuildThreads;   // rows of a lane
+  extern __shared__ int32_t lds2[];
+  int32_t *total = lds2;                            // a.n_bins
+  int32_t *queue = lds2 + ((a.n_bins + 3) & ~3);    // with predicates only
+  __shared__ uint16_t stage[kChunk] __attribute__((aligned(16)));
+  __shared__ int32_t hist[kSegMaxBins], start[kSegMaxBins + 1];
+  __shared__ int32_t s_qn;
+  const Job2d job{P};
+  const int d = a.d, nbr = a.nbr;
+  const bool pow2 = P.bm1.pow2 && P.bm.pow2 && (KD < 3 || kx.bm3.pow2) &&
+                    (KD < 4 || kx.bm4.pow2);
+  for (int j = threadIdx.x; j < a.n_bins; j += kBuildThreads) total[j] = 0;
+  if (threadIdx.x < kSegMaxBins) hist[threadIdx.x] = 0;
+  const int64_t r0 = a.row0 + (int64_t)blockIdx.x * a.rows_per_block;
+  const int64_t r1 = min(a.row1, r0 + a.rows_per_block);
+  const bool dense = P.n_preds == 0;
+  uint64_t sel = 0;
+  int qn = 0;              // rows waiting: queue[0, qn), or done + [0, qn)
+  int64_t done = 0;        // dense: rows of the block already hashed
+  int used = 0;            // chunks of the block
+  __syncthreads();
+  for (int64_t base = r0; base < r1; base += kBuildTile) {
+    const int nt = (int)min((int64_t)kBuildTile, r1 - base);
+    const int before = qn;
+    if (dense)
+      qn += nt;
+    else
+      qn = compact_tile<Job2d, kBuildRowsPerThread>(job, base, nt, P.n_preds, queue,
+                                                    &s_qn, before, (int)(base - r0));
+    sel += (uint64_t)(qn - before);
+    const bool last = base + kBuildTile >= r1;
+    while (qn >= kChunk || (last && qn > 0)) {   // block-uniform
+      const int n = min(qn, kChunk);
+      const SegRows rows{dense ? nullptr : queue, r0 + done, n};
+      uint32_t x[4][R];
+      uint32_t high = 0;
+#pragma unroll
+      for (int s = 0; s < KD; ++s) {
+        uint64_t xx[R];
+        rows.load(P.keys[s], 0, xx);
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+          x[s][k] = (uint32_t)xx[k];
+          high |= (uint32_t)(xx[k] >> 32);
+        }
+      }
+      const bool wide = __any(high != 0);
+      const int64_t chunk = (int64_t)blockIdx.x * a.block_chunks + used++;
+      for (int i = 0; i < d; ++i) {
+        uint32_t rec[R];      // tile << 16 | record
+        uint32_t rank[R];
+        seg_records<0, KD>(P, a, kx, rows, i, wide, pow2, x, rec);
+        // (apart: interleaved, the two halves' values do not fit the registers)
+        __builtin_amdgcn_sched_barrier(0);
+        seg_records<4, KD>(P, a, kx, rows, i, wide, pow2, x, rec);
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+          rank[k] = (int)threadIdx.x + k * kBuildThreads < n
+                        ? (uint32_t)atomicAdd(&hist[rec[k] >> 16], 1) : 0u;
+        __syncthreads();
+        if (threadIdx.x < 64) {   // starts of the tiles, four to a lane
+          int32_t c[4], sum = 0;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            c[u] = hist[4 * threadIdx.x + u];
+            sum += c[u];
+          }
+          int32_t run = sum;
+#pragma unroll
+          for (int o = 1; o < 64; o <<= 1) {
+            const int32_t v = __shfl_up(run, o);
+            run += (int)threadIdx.x >= o ? v : 0;
+          }
+          run -= sum;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int j = 4 * threadIdx.x + u;
+            start[j] = run;
+            run += c[u];
+            if (j < nbr) total[i * nbr + j] += c[u];
+            hist[j] = 0;
+          }
+          if (threadIdx.x == 63) start[kSegMaxBins] = run;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+          if ((int)threadIdx.x + k * kBuildThreads < n)
+            stage[start[rec[k] >> 16] + rank[k]] = (uint16_t)rec[k];
+        __syncthreads();
+        // (stores only after the last barrier: a barrier waits for them)
+        const int64_t at = chunk * d + i;
+        if ((int)threadIdx.x <= nbr)
+          a.off[at * (nbr + 1) + threadIdx.x] = (uint16_t)start[threadIdx.x];
+        const uint4 *from = reinterpret_cast<const uint4 *>(stage);
+        uint4 *to = reinterpret_cast<uint4 *>(a.rec + at * kChunk);
+        for (int j = threadIdx.x; j * 8 < n; j += kBuildThreads) to[j] = from[j];
+      }
+      qn -= n;
+      if (dense) {
+        done += n;
+      } else if (qn > 0) {   // at most kBuildTile rows wait
+        int32_t keep[kBuildRowsPerThread];
+#pragma unroll
+        for (int k = 0; k < kBuildRowsPerThread; ++k) {
+          const int q = threadIdx.x + k * kBuildThreads;
+          keep[k] = q < qn ? queue[n + q] : 0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kBuildRowsPerThread; ++k) {
+          const int q = threadIdx.x + k * kBuildThreads;
+          if (q < qn) queue[q] = keep[k];
+        }
+      }
+      __syncthreads();   // stage and the queue are reused
+    }
+  }
+  // chunks that selected rows did not fill have empty segments
+  for (int64_t j = (int64_t)used * d * (nbr + 1) + threadIdx.x;
+       j < (int64_t)a.block_chunks * d * (nbr + 1); j += kBuildThreads)
+    a.off[(int64_t)blockIdx.x * a.block_chunks * d * (nbr + 1) + j] = 0;
+  for (int j = threadIdx.x; j < a.n_bins; j += kBuildThreads)
+    if (total[j]) atomicAdd(a.bin_total + j, total[j]);
+  if (P.count_selected && threadIdx.x == 0 && sel)
+    atomicAdd(reinterpret_cast<unsigned long long *>(P.n_selected),
+              (unsigned long long)sel);
+}
+
+// Parts of at most 1 / (4 n_cu) of the records (grid: n_cu workgroups): the
+// records of a frequent key are in one tile per sketch row (one key has 6 % of
+// the 36M rows above), and its workgroup would outlast the others; parts twice
+// as large cost seg_tile_kernel a tenth more, half as large nothing less.  Every workgroup computes the plan,
+// the first one writes it; the tiles of several parts are zeroed here.
+template <typename C>
+__global__ __launch_bounds__(kBuildThreads) void seg_plan_kernel(
+    const SegArgs a, C *counters, int32_t accumulate) {
+  constexpr int kPer = kSegMaxTotal / kBuildThreads;
+  __shared__ int32_t part[kBuildThreads];
+  __shared__ unsigned long long s_sum;
+  if (threadIdx.x == 0) s_sum = 0;
+  __syncthreads();
+  const int per = (a.n_bins + kBuildThreads - 1) / kBuildThreads;
+  const int j0 = threadIdx.x * per, j1 = min(a.n_bins, j0 + per);
+  int32_t t[kPer];
+  int64_t sum = 0;
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    t[u] = j0 + u < j1 ? a.bin_total[j0 + u] : 0;
+    sum += t[u];
+  }
+  atomicAdd(&s_sum, (unsigned long long)sum);
+  __syncthreads();
+  const int32_t most =
+      (int32_t)max((int64_t)16384, (int64_t)(s_sum / (4 * gridDim.x)) + 1);
+  int32_t n = 0;
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    t[u] = j0 + u < j1 ? max(1, (t[u] + most - 1) / most) : 0;
+    n += t[u];
+  }
+  part[threadIdx.x] = n;
+  __syncthreads();
+  for (int o = 1; o < kBuildThreads; o <<= 1) {
+    const int32_t v = (int)threadIdx.x >= o ? part[threadIdx.x - o] : 0;
+    __syncthreads();
+    part[threadIdx.x] += v;
+    __syncthreads();
+  }
+  if (blockIdx.x == 0) {
+    int32_t at = part[threadIdx.x] - n;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+      for (int q = 0; q < t[u]; ++q)
+        if (at < a.max_items) a.items[at++] = SegItem{j0 + u, q, t[u], 0};
+    if (threadIdx.x == kBuildThreads - 1)
+      *a.n_items = min(part[threadIdx.x], a.max_items);
+  }
+  if (accumulate) return;
+  for (int j = blockIdx.x; j < a.n_bins; j += gridDim.x) {
+    if (a.bin_total[j] <= most) continue;   // one part: written whole
+    const int i = j / a.nbr, j1a = (j % a.nbr) << a.r_shift;
+    const int words = min(1 << a.r_shift, a.w1 - j1a) * a.w2;
+    C *dst = counters + ((int64_t)i * a.w1 + j1a) * a.w2;
+    for (int k = threadIdx.x; k < words; k += kBuildThreads) dst[k] = 0;
+  }
+}
+
+template <typename C>
+__global__ __launch_bounds__(kBuildThreads, 8) void seg_tile_kernel(
+    const SegArgs a, C *counters, int32_t accumulate) {
+  extern __shared__ int32_t lds2[];
+  int32_t *tile = lds2;
+  // consecutive tiles on one XCD (workgroups go round the eight): their
+  // segments share cache lines, and the workgroups walk the chunks together
+  const int n_items = *a.n_items, share = (n_items + 7) / 8;
+  const int slot = blockIdx.x >> 3, item = (blockIdx.x & 7) * share + slot;
+  if (slot >= share || item >= n_items) return;
+  const SegItem it = a.items[item];
+  const int i = it.tile / a.nbr, jb = it.tile - i * a.nbr;
+  const int j1a = jb << a.r_shift;
+  const int words = min(1 << a.r_shift, a.w1 - j1a) * a.w2;
+  for (int j = threadIdx.x; j < words; j += kBuildThreads) tile[j] = 0;
+  const int64_t nc = (int64_t)a.n_blocks * a.block_chunks;
+  const int c0 = (int)(nc * it.part / it.parts);
+  const int c1 = (int)(nc * (it.part + 1) / it.parts);
+  __syncthreads();
+  // a wave takes kSeg chunks' segments at once, a segment by its 64 lanes:
+  // the segments' first loads are in flight together
+  constexpr int kSeg = 16;
+  const int lane = threadIdx.x & 63;
+  auto add = [&](uint32_t r) { atomicAdd(&tile[r >> 1], 1 - 2 * (int)(r & 1u)); };
+  for (int c = c0 + (int)(threadIdx.x >> 6) * kSeg; c < c1;
+       c += kBuildThreads / 64 * kSeg) {
+    const int mine = c + (lane & (kSeg - 1));
+    int32_t v = 0;   // starts in lanes 0 .. 15, ends in 16 .. 31
+    if (mine < c1 && lane < 2 * kSeg)
+      v = a.off[((int64_t)mine * a.d + i) * (a.nbr + 1) + jb + (lane >= kSeg)];
+    uint32_t r[kSeg], r2[kSeg];
+#pragma unroll
+    for (int u = 0; u < kSeg; ++u) {
+      const uint16_t *src = a.rec +
+                            ((int64_t)min(c + u, c1 - 1) * a.d + i) * kSegChunk +
+                            __builtin_amdgcn_readlane(v, u);
+      r[u] = src[lane];
+      r2[u] = src[64 + lane];
+    }
+#pragma unroll
+    for (int u = 0; u < kSeg; ++u) {
+      const int32_t len = __builtin_amdgcn_readlane(v, kSeg + u) -
+                          __builtin_amdgcn_readlane(v, u);
+      if (lane < len) add(r[u]);
+      if (64 + lane < len) add(r2[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kSeg; ++u) {
+      const int32_t s = __builtin_amdgcn_readlane(v, u);
+      const int32_t len = __builtin_amdgcn_readlane(v, kSeg + u) - s;
+      if (len <= 128) continue;   // wave-uniform
+      const uint16_t *src = a.rec + ((int64_t)(c + u) * a.d + i) * kSegChunk + s;
+      for (int q = 128 + lane; q - lane < len; q += 256) {
+        uint32_t t[4];
+#pragma unroll
+        for (int z = 0; z < 4; ++z) t[z] = src[q + 64 * z];
+#pragma unroll
+        for (int z = 0; z < 4; ++z)
+          if (q + 64 * z < len) add(t[z]);
+      }
+    }
+  }
+  __syncthreads();
+  C *dst = counters + ((int64_t)i * a.w1 + j1a) * a.w2;
+  if (it.parts > 1) {
+    for (int j = threadIdx.x; j < words; j += kBuildThreads)
+      if (tile[j]) add_counter<C>(dst + j, tile[j]);
+  } else if (accumulate) {
+    for (int j = threadIdx.x; j < words; j += kBuildThreads) dst[j] += (C)tile[j];
+  } else {
+    for (int j = threadIdx.x; j < words; j += kBuildThreads)
+      __builtin_nontemporal_store((C)tile[j], dst + j);
+  }
+}
+
+template <typename C>
+static hipError_t seg_sum(const SegArgs &a, C *counters, int accumulate, int n_cu,
+                          hipStream_t st) {
+  hipLaunchKernelGGL(seg_plan_kernel<C>, dim3(n_cu), dim3(kBuildThreads), 0, st, a,
+                     counters, accumulate);
+  hipLaunchKernelGGL(seg_tile_kernel<C>, dim3(a.max_items), dim3(kBuildThreads),
+                     (size_t)(a.w2 << a.r_shift) * 4, st, a, counters, accumulate);
+  return hipGetLastError();
+}
+
+hipError_t launch_scan2d_segments(const BuildParams &P, const SegArgs &a,
+                                  const KdDims &kx, int accumulate, int n_cu,
+                                  hipStream_t st) {
+  const size_t lds = (size_t)((a.n_bins + 3) & ~3) * 4 +
+                     (P.n_preds ? (size_t)(kSegChunk + kBuildTile) * 4 : 0);
+  auto scan = kx.kd == 2 ? seg_scan_kernel<2>
+              : kx.kd == 3 ? seg_scan_kernel<3> : seg_scan_kernel<4>;
+  hipLaunchKernelGGL(scan, dim3(a.n_blocks), dim3(kBuildThreads), lds, st, P, a, kx);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return P.counter_bits == 32
+             ? seg_sum(a, reinterpret_cast<int32_t *>(P.counters[0]), accumulate,
+                       n_cu, st)
+             : seg_sum(a, reinterpret_cast<int64_t *>(P.counters[0]), accumulate,
+                       n_cu, st);
+}
+
 constexpr int kChainThreads = 512;
 constexpr int kChainMaxW2 = 16384;
 constexpr int kChainPerLane = kChainMaxW2 / kChainThreads;  // B values per lane

@@ -65,6 +65,32 @@ struct TensorArgs {
   int32_t counter_bits, d, w_max, pad;
 };
 
+// Segmented build (few tiles per sketch row, see partition.hip): chunks of at
+// most kSegChunk selected rows, each chunk's records of a sketch row grouped
+// by tile in the chunk's own region.
+constexpr int kSegMaxBins = 256;       // tiles per sketch row
+constexpr int kSegMaxTotal = 8192;     // tiles
+constexpr int kSegPad = 1024;          // records that may be read past the last
+
+constexpr int kSegChunk = 8192;        // rows of a chunk, their keys in registers
+
+struct SegItem {
+  int32_t tile, part, parts, pad;
+};
+
+struct SegArgs {
+  int32_t d, w1, w2, r_shift;
+  int32_t nbr, n_bins, n_blocks, max_items;
+  int64_t row0, row1;            // rows of this batch
+  int64_t rows_per_block;        // a multiple of kBuildTile
+  int32_t block_chunks, pad;     // chunk regions per block
+  int32_t *bin_total;            // [n_bins] records (zeroed)
+  int32_t *n_items;
+  SegItem *items;                // [max_items]
+  uint16_t *off;                 // [chunk][d][nbr + 1] segment starts
+  uint16_t *rec;                 // [chunk][d][chunk rows]
+};
+
 struct Bin2dArgs {
   int32_t d, w1, w2, r_shift;
   int32_t nbr, n_bins, n_blocks, pad;

@@ -285,6 +285,64 @@ def test_build_kd_matches_oracle(oracle, k, widths, bits, preds_on, n):
     assert np.array_equal(T.cpu().numpy().astype(np.int64), o)
 
 
+@gpu
+@pytest.mark.parametrize("widths,d,bits,preds_on,keys_are", [
+    ([512, 512], 3, 32, False, "zipf"),           # 16 tiles of a row, one heavy
+    ([255, 16384], 2, 32, True, "zipf"),          # one matrix row to a tile
+    ([64, 50, 20], 3, 64, True, "wide"),          # widths not powers of two
+    ([16, 16, 16, 16], 2, 32, False, "wide"),
+    ([7, 3], 5, 64, True, "one"),                 # every row in one counter
+    ([300, 100], 2, 32, True, "none"),            # no row selected
+])
+def test_build_kd_segments(widths, d, bits, preds_on, keys_are):
+    """The segmented build of large tables against the binned one, which a
+    small record budget selects; a second call adds to the first."""
+    import os
+    torch = _torch()
+    from paper_2102_02440_amd import compass as C
+    _say("build_kd segments", widths, d, bits, preds_on, keys_are)
+    rng = np.random.default_rng(sum(widths) + d)
+    n, k = (1 << 21) + 4097, len(widths)
+    if keys_are == "wide":
+        keys = [rng.integers(-2**62, 2**62, n) if m % 2 else rng.integers(0, 2**33, n)
+                for m in range(k)]
+    elif keys_are == "one":
+        keys = [np.full(n, 12345, np.int64)] * k
+    else:
+        keys = [W.fk_column(rng, n, 300_000, 1.05, rng.permutation(300_000)).astype(np.int32)
+                for _ in range(k)]
+    attr = torch.from_numpy(rng.integers(0, 100, n).astype(np.int32)).cuda()
+    lo = 200 if keys_are == "none" else 37
+    preds = [{"col": 0, "kind": "range", "lo": lo, "hi": 300}] if preds_on else []
+    seeds = list(W.draw_seeds(rng, k, d))
+    dk = [torch.from_numpy(x).cuda() for x in keys]
+    ct = torch.int32 if bits == 32 else torch.int64
+
+    def build(budget, accumulate, T, nsel):
+        if budget:
+            os.environ["COMPASS_2D_RECORD_BYTES"] = str(budget)
+        try:
+            C.sketch_build_kd(n, [attr] if preds_on else [], preds, dk, seeds, T, nsel, d,
+                              widths, counter_bits=bits, accumulate=accumulate)
+            torch.cuda.synchronize()
+        finally:
+            if budget:
+                del os.environ["COMPASS_2D_RECORD_BYTES"]
+
+    assert "COMPASS_2D_RECORD_BYTES" not in os.environ
+    out = []
+    for budget in (None, 4 * d * 1_000_000):
+        T = torch.full((d,) + tuple(widths), 7, dtype=ct, device="cuda")
+        nsel = torch.full((1,), 3, dtype=torch.int64, device="cuda")
+        build(budget, False, T, nsel)
+        first = T.cpu()
+        build(budget, True, T, nsel)
+        assert torch.equal(T.cpu(), 2 * first)
+        out.append((first, int(nsel.item())))
+    assert torch.equal(out[0][0], out[1][0])
+    assert out[0][1] == out[1][1]
+
+
 def _tree_case(rng, kind):
     """(n_tables, edge_u, edge_v, widths, per-table key columns by edge)."""
     if kind == "star":        # center 0 with three leaves
