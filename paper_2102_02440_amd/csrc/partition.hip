@@ -558,11 +558,16 @@ __global__ __launch_bounds__(kBuildThreads) void seg_scan_kernel(
   for (int64_t base = r0; base < r1; base += kBuildTile) {
     const int nt = (int)min((int64_t)kBuildTile, r1 - base);
     const int before = qn;
-    if (dense)
+    if (dense) {
       qn += nt;
-    else
-      qn = compact_tile<Job2d, kBuildRowsPerThread>(job, base, nt, P.n_preds, queue,
-                                                    &s_qn, before, (int)(base - r0));
+    } else {
+      // (inlined: a call would take the parameters' address, and with it a
+      // copy of them to scratch memory)
+      uint32_t cur[kBuildRowsPerThread];
+      load_first_pred<Job2d, kBuildRowsPerThread>(job, base, nt, cur);
+      [[clang::always_inline]] qn = compact_tile_loaded<Job2d, kBuildRowsPerThread>(
+          job, base, nt, P.n_preds, queue, &s_qn, before, (int)(base - r0), cur);
+    }
     sel += (uint64_t)(qn - before);
     const bool last = base + kBuildTile >= r1;
     while (qn >= kChunk || (last && qn > 0)) {   // block-uniform

@@ -139,7 +139,7 @@ __device__ __forceinline__ void load_first_pred(const J &job, int64_t base,
 // compact_tile with the first predicate's values already loaded (by
 // load_first_pred for the same tile); n_preds >= 1.
 template <class J, int kRowsPerThread>
-__device__ __forceinline__ int compact_tile_loaded(const J &job, int64_t base, int nt,
+__device__ int compact_tile_loaded(const J &job, int64_t base, int nt,
                                    int n_preds, int32_t *queue, int32_t *s_qn,
                                    int start, int bias,
                                    uint32_t (&cur)[kRowsPerThread]) {
@@ -193,7 +193,7 @@ __device__ __forceinline__ int compact_tile_loaded(const J &job, int64_t base, i
 // predicates every row qualifies; the queue is then not used and nt is
 // returned.  Every thread of the block must call it.
 template <class J, int kRowsPerThread>
-__device__ __forceinline__ int compact_tile(const J &job, int64_t base, int nt, int n_preds,
+__device__ int compact_tile(const J &job, int64_t base, int nt, int n_preds,
                             int32_t *queue, int32_t *s_qn, int start = 0,
                             int bias = 0) {
   if (n_preds == 0) return nt;
