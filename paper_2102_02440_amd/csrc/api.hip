@@ -442,6 +442,7 @@ static compass_status build_two_phase(const BuildParams &base,
     }
     FlushCtl fc;
     memset(&fc, 0, sizeof fc);
+    fc.n_cu = n_cu;
     fc.count = count;
     fc.ticket = ticket;
     fc.cap = pl.cap;

@@ -127,7 +127,7 @@ struct FlushCtl {
   int64_t cap;                 // survivors the buffer holds per sketch
   int64_t need;                // rows of the next batch
   int32_t force;
-  int32_t pad;
+  int32_t n_cu;                // compute units (one hashing workgroup each)
 };
 
 // A run of slice seeds written to device memory by one small launch.
