@@ -790,7 +790,7 @@ static compass_status sketch_build_impl(
       if (waste == 0) break;
     }
   }
-  const int n_groups_total = (S + per_group - 1) / per_group;
+  int n_groups_total = (S + per_group - 1) / per_group;
 
   // chunks: two whole waves of the resident workgroup slots, else one
   // (whole waves, so that no slot runs one more workgroup than the others),
@@ -812,6 +812,37 @@ static compass_status sketch_build_impl(
       chunks = std::min(c, std::max<int64_t>(1, tiles / 8));
       break;
     }
+  }
+  // Tables too small to fill the CUs that way: chunks down to one tile and
+  // smaller slice groups, by the time of the rounds (a tile's updates at 2.4
+  // per ns and CU, 1.2 for widths that are no power of two; clearing and
+  // writing the group's counters; 3 us) and of the slab's reduction.  0.2M
+  // and 1.6M rows of 15 slices of 3000 counters: 189 and 188 us at eight
+  // tiles, 43 us each on average this way; 2000 rows of 7 slices: 34 and 13.
+  if (chunks * n_groups_total < n_cu && !serial) {
+    const double per_ns = base.bm.pow2 ? 2.4 : 1.2;
+    double least = 0;
+    int64_t best_c = chunks;
+    int best_g = per_group;
+    for (int ng = n_groups_total; ng <= std::min(S, kMaxLaunchGroups); ++ng) {
+      const int g = (S + ng - 1) / ng;
+      const int groups = (S + g - 1) / g;
+      for (int64_t c : {chunks, (tiles + 3) / 4, (tiles + 1) / 2, tiles}) {
+        if (c < chunks) continue;
+        const double rounds = (double)((c * groups + n_cu - 1) / n_cu);
+        const double t = rounds * ((double)((tiles + c - 1) / c) * kScanTile * g / per_ns +
+                                   0.25 * g * w + 3000) +
+                         0.0016 * (double)c * S * w;
+        if (least == 0 || t < 0.95 * least) {
+          least = t;
+          best_c = c;
+          best_g = g;
+        }
+      }
+    }
+    chunks = best_c;
+    per_group = best_g;
+    n_groups_total = (S + per_group - 1) / per_group;
   }
   const size_t slab_row = (size_t)S * w * 4;
   const size_t slab_cap = ar.fixed ? ar.fixed_bytes : ((size_t)1 << 30);
