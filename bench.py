@@ -961,12 +961,12 @@ def run_agms(args):
 
     n_sel = [int(x[6].item()) for x in tabs]
     joins = [len(q.incident(t)) for t in range(len(q.tables))]
-    # per (selected row, basic sketch): per join one sign = 3 Horner steps
-    # of 6 operations + 3 for the residue's low bit + 1 multiply into the
-    # product; then 1 add
-    ops = sum(n * K * (22 * j + 1) for n, j in zip(n_sel, joins))
+    # bytes every build must read: predicate columns, distinct key columns of
+    # the selected rows (the signs of a key are evaluated once, so the
+    # evaluations per row and sketch are no count of the work)
+    alg_bytes = sum(algorithmic_work(q, n_sel, with_preds=p)[0] for p in (False, True))
     k_s = kms / args.steps / 1e3
-    tops = ops / k_s / 1e12
+    gbs = alg_bytes / k_s / 1e9
     rows = sum(tb.n_rows for tb in q.tables)
     e_a, e_f = float(est.item()), float(est_f[0].item())
     out = {"metric": METRIC,
@@ -976,9 +976,10 @@ def run_agms(args):
            "config": {"workload": "AGMS baseline on the 6a-shaped query: 5 tables "
                                   "(47.1M rows), r x b = 7 x 16 composed sketches",
                       "selected_rows": n_sel, "parallelism": "single-gpu"},
-           "roofline": {"bound": "alu", "achieved": tops, "peak": ALU_PEAK_TOPS,
-                        "unit": "TOP/s", "frac": tops / ALU_PEAK_TOPS, "traffic": None,
-                        "kernel": "agms_build", "launches_per_step": kn / args.steps,
+           "roofline": {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS,
+                        "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS, "traffic": None,
+                        "kernel": "agms_build", "alg_bytes_per_step": alg_bytes,
+                        "launches_per_step": kn / args.steps,
                         "kernel_ms_per_step": k_s * 1e3},
            "fast_agms_build_ms": fast_ms,
            "agms_over_fast_agms_build_time": dt * 1e3 / fast_ms,
@@ -1146,15 +1147,15 @@ def run_job6a(args):
     def step_keep():
         out_last[:] = [step()]
 
-    dt1, scan_prof = timed_steps(C, torch, step_keep, args.steps, "scan_sketch")
+    dt1, count_prof = timed_steps(C, torch, step_keep, args.steps, "count")
     dt = dt1 * args.steps
     row_est, est, flags = out_last[0]
     # the other kernels' times: a second pass with every kernel's events
     prof = profiled_steps(C, torch, step, args.steps,
-                          ["fill_zero", "scan_sketch", "slab_reduce", "wide_compact",
-                           "wide_hash", "sort_rows", "node", "tri_order", "tri_lane",
-                           "generic", "finish"])
-    prof["scan_sketch"] = scan_prof
+                          ["fill_zero", "count", "weighted_scan", "scan_sketch",
+                           "slab_reduce", "wide_compact", "wide_hash", "sort_rows",
+                           "node", "tri_order", "tri_lane", "generic", "finish"])
+    prof["count"] = count_prof
     # the 19 estimates alone, without any timing event: wall time per call
     torch.cuda.synchronize()
     a_ = time.perf_counter()
@@ -1176,33 +1177,34 @@ def run_job6a(args):
     rows_per_step = sum(tb.n_rows for tb in q.tables)
     # the metric counts filtered rows sketched: the rows that qualified
     value = sum(n_sel) * args.steps / dt
-    # the fused scan kernel builds the tables without predicates; the
-    # tables with predicates take the two-phase build
+    # the counted build takes the tables without predicates (their keys
+    # repeat), the two-phase build those with predicates
     alg_bytes, updates = algorithmic_work(q, n_sel, with_preds=False)
     sel_bytes, sel_updates = algorithmic_work(q, n_sel, with_preds=True)
-    build_ms_step = sum(prof[k][1] for k in ["fill_zero", "scan_sketch", "slab_reduce",
+    build_ms_step = sum(prof[k][1] for k in ["fill_zero", "count", "weighted_scan",
+                                             "scan_sketch", "slab_reduce",
                                              "wide_compact", "wide_hash"]) / args.steps
     est_ms_step = sum(prof[k][1] for k in ["sort_rows", "node", "tri_order",
                                            "tri_lane", "generic", "finish"]) / args.steps
     kernel_ms = {k: v[1] / args.steps for k, v in prof.items()}
-    scan_s = kernel_ms["scan_sketch"] / 1e3
-    scan_tops = updates * OPS_PER_HASH_UPDATE / scan_s / 1e12
-    hbm_view = {"kernel": "scan_sketch", "alg_bytes_per_step": alg_bytes,
-                "achieved_gbs": alg_bytes / scan_s / 1e9, "peak_gbs": HBM_PEAK_GBS,
-                "frac": alg_bytes / scan_s / 1e9 / HBM_PEAK_GBS}
-    # the scan is the dominant kernel of the step (the estimate kernels
-    # together take a quarter of its time)
-    roofline = {"bound": "alu", "achieved": scan_tops, "peak": ALU_PEAK_TOPS,
-                "unit": "TOP/s", "frac": scan_tops / ALU_PEAK_TOPS,
-                "traffic": measured_traffic("scan_sketch_traffic_job6a.md",
-                                            SCAN_SOURCES),
-                "kernel": "scan_sketch", "hash_updates_per_step": updates,
-                "ops_per_hash_update": OPS_PER_HASH_UPDATE}
+    # the counting passes (partition by key range, LDS counts, distinct keys
+    # listed) are the step's largest share; the columns they read once are
+    # their algorithmic bytes
+    count_s = kernel_ms["count"] / 1e3
+    fused_s = (kernel_ms["count"] + kernel_ms["weighted_scan"]
+               + kernel_ms["scan_sketch"]) / 1e3
+    gbs = alg_bytes / count_s / 1e9
+    roofline = {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS,
+                "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS, "traffic": None,
+                "kernel": "count", "alg_bytes_per_step": alg_bytes}
     roofline["launches_per_step"] = prof[roofline["kernel"]][0] / args.steps
     roofline["kernel_ms_per_step"] = kernel_ms[roofline["kernel"]]
     two_s = (kernel_ms["wide_compact"] + kernel_ms["wide_hash"]) / 1e3
-    other = {"scan_sketch": {"alu_tops": scan_tops, "hash_updates_per_s": updates / scan_s},
-             "scan_sketch_hbm": hbm_view,
+    other = {"counted_build": {"kernels": ["count", "weighted_scan", "scan_sketch"],
+                               "note": "updates of hashing every row, over the time "
+                                       "of counting and hashing each distinct key once",
+                               "row_updates_per_step": updates,
+                               "row_updates_per_s": updates / fused_s},
              "two_phase": {"kernels": ["wide_compact", "wide_hash"],
                            "note": "second stream beside the fused scans: the "
                                    "kernels' event spans include time spent "
