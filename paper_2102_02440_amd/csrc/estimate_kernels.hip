@@ -423,6 +423,8 @@ __device__ __forceinline__ T block_scan_incl(T v, T *sh) {
   if (lane == (kSuffix ? 0 : 63)) sh[wave] = v;
   __syncthreads();
   T add = 0;
+  // (four at a time: sixteen 128-bit totals at once would spill the sweeps)
+#pragma unroll 4
   for (int k = 0; k < kW; ++k) {
     const T y = sh[k];
     if (kSuffix ? k > wave : k < wave) add += y;
@@ -697,8 +699,7 @@ __device__ void node_sweeps(const NodeTask &T, const NodeRec *rec, int L,
 __global__ __launch_bounds__(kNodeThreads) void node_kernel(
     const NodeTask *tasks, EstBuffers B) {
   __shared__ u128 sh[kNodeThreads / 64];
-  const NodeTask *Tg = tasks + blockIdx.x;
-  const NodeTask T = *Tg;
+  const NodeTask &T = tasks[blockIdx.x];
   if (!T.guard.on) return;  // uniform
   const int row = blockIdx.y;
   const int w = B.w;
