@@ -136,6 +136,18 @@ inline int counted_bins(int64_t n_rows, int slices, bool also = false) {
   return (int)std::min<double>(bins, kCntMaxBins);
 }
 
+// A workgroup's decision on a word that other workgroups of the same launch
+// may be writing: one lane reads it and every lane acts on what that lane
+// saw.  Waves that read for themselves may see different values, and one that
+// leaves no longer takes part in the barriers of those that stay.  (constexpr:
+// callable on the host and on the device.)
+template <class Load, class Barrier>
+constexpr bool block_reads(uint32_t *shared, bool reader, Load load, Barrier barrier) {
+  if (reader) *shared = load();
+  barrier();
+  return *shared != 0;
+}
+
 // Tiles of a partitioned column: workgroups of tiles_per_wg tiles each,
 // wg_per_sg workgroups per super-group, at most kCntMaxSg super-groups.
 struct CountTiles {

@@ -297,8 +297,12 @@ __global__ __launch_bounds__(kCntThreads) __attribute__((amdgpu_waves_per_eu(8, 
   extern __shared__ uint16_t s_rec[];        // rec_stride records
   __shared__ uint32_t s_bin[kCntMaxBins + 1];  // last used: keys of no bin
   __shared__ uint32_t s_wave[kCntThreads / 64];
-  __shared__ uint32_t s_stop;
-  if (A.st[blockIdx.y].bad || (int)blockIdx.x * A.tiles_per_wg >= A.n_tiles) return;
+  __shared__ uint32_t s_bad, s_stop;
+  if ((int)blockIdx.x * A.tiles_per_wg >= A.n_tiles) return;   // uniform
+  if (block_reads(&s_bad, threadIdx.x == 0,
+                  [&] { return column_bad(A.st + blockIdx.y); },
+                  [] { __syncthreads(); }))
+    return;
   if (A.c[blockIdx.y].dtype == kDtI32)
     partition_tiles<int32_t>(A, s_rec, s_bin, s_wave, &s_stop);
   else
