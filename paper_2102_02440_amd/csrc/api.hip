@@ -445,6 +445,7 @@ static compass_status build_two_phase(const BuildParams &base,
     fc.n_cu = n_cu;
     fc.count = count;
     fc.ticket = ticket;
+    fc.chunks = reinterpret_cast<int32_t *>(ticket + 1);
     fc.cap = pl.cap;
     fc.need = r1 < n_rows ? std::min(pl.batch, n_rows - r1) : 0;
     fc.force = r1 >= n_rows;

@@ -34,6 +34,7 @@
 #include <algorithm>
 
 #include "build_params.hpp"
+#include "build_plan.hpp"
 #include "device_math.hpp"
 #include "scan_common.hpp"
 
@@ -212,40 +213,14 @@ __global__ __launch_bounds__(kBuildThreads) __attribute__((amdgpu_waves_per_eu(8
 // int32 registers and clears them.  One hash per update even at w = 65536.
 constexpr int kWidePiece = 32767;
 constexpr int kWidePairsPerLane = 32;   // 32768 words / 1024 lanes
-constexpr int64_t kWideMinChunk = 16384;  // survivors per hashing chunk
-constexpr int kWideRange = 2 * kWidePairsPerLane * kBuildThreads;  // 65536
+static_assert(kWideRange == 2 * kWidePairsPerLane * kBuildThreads, "pairs of a workgroup");
 constexpr int kWideKeys = 4;  // survivors per lane in flight (fast path)
 
-// Chunks the n survivors are hashed in: at least kWideMinChunk survivors each
-// (a chunk's fixed cost is clearing, folding and writing w counters), at most
-// `chunks`.  Where that is more than one round of the CUs, of the counts that
-// fill one to four rounds the one with the least time -- rounds of items (0.31
-// ns per survivor, 0.2 ns per counter, 2 us), then the reduction (0.4 ns per
-// KB of slab).  1.5M survivors of 66 slices of 65,536 counters: the 15 chunks
-// of the best fill took 180 us and 101 to reduce, the fewer picked here take
-// 143 and 67.  The reduction computes the same count.
+// hash_chunks of a flush, in a scalar register (n is a loaded value: the
+// loops' bounds would be the vector unit's).
 __device__ __forceinline__ int64_t active_chunks(int64_t n, int64_t chunks, int n_slices,
                                                  int w, int n_cu) {
-  const int64_t need = (n + kWideMinChunk - 1) / kWideMinChunk;
-  const int most = (int)(need < 1 ? 1 : (need < chunks ? need : chunks));
-  const int items = n_slices * ((w + kWideRange - 1) / kWideRange);
-  if (most * items <= n_cu) return most;
-  int best = 1;
-  float best_cost = 3.0e38f;
-#pragma unroll
-  for (int k = 1; k <= 4; ++k) {
-    const int c = min(most, max(1, k * n_cu / items));
-    const int rounds = (c * items + n_cu - 1) / n_cu;
-    const float cost =
-        (float)rounds * (0.31f * (float)n / (float)c + 0.2f * (float)min(w, kWideRange) + 2000.f) +
-        0.0015f * (float)c * (float)n_slices * (float)w;
-    if (cost < best_cost) {
-      best_cost = cost;
-      best = c;
-    }
-  }
-  // (float arithmetic is the vector unit's: the loops' bounds stay scalar)
-  return __builtin_amdgcn_readfirstlane(best);
+  return __builtin_amdgcn_readfirstlane(hash_chunks(n, chunks, n_slices, w, n_cu));
 }
 
 // A flush (hashing of the survivors buffered so far, then the slab
@@ -267,6 +242,7 @@ __global__ __launch_bounds__(kBuildThreads) void wide_hash_kernel(
   if (!flush_due(fc, n)) return;  // the buffer takes the next batch
   const int64_t cap = fc.cap;
   const int64_t act = active_chunks(n, chunks, n_slices, (int)bm.w, fc.n_cu);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *fc.chunks = (int32_t)act;
   // The act * n_slices * ranges items that carry work are numbered with
   // the slice fastest and split into kXcds contiguous runs, one per XCD
   // (workgroup b runs on XCD b mod kXcds): the d slices of one sketch read
@@ -446,7 +422,7 @@ __global__ void slab_reduce_kernel(const int32_t *__restrict__ slab,
   if (fc.count) {
     const int64_t n = (int64_t)*fc.count;
     if (!flush_due(fc, n)) return;
-    chunks = active_chunks(n, chunks, n_slices, w, fc.n_cu);
+    chunks = *fc.chunks;
   }
   const int64_t total = (int64_t)n_slices * w;
   if (vec4) {

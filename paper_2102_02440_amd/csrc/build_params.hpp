@@ -124,6 +124,7 @@ static_assert(sizeof(BuildParams) <= 4096, "kernel arguments must stay small");
 struct FlushCtl {
   unsigned long long *count;   // survivors in the buffer (device)
   unsigned int *ticket;        // workgroups of the reduction done (device)
+  int32_t *chunks;             // slab rows the hashing fills (device)
   int64_t cap;                 // survivors the buffer holds per sketch
   int64_t need;                // rows of the next batch
   int32_t force;

@@ -102,6 +102,43 @@ inline TwoPhasePlan plan_two_phase(int64_t n_rows, int n_sketches, int d,
   return p;
 }
 
+// Chunks the n survivors of a flush are hashed in: at least kWideMinChunk
+// survivors each (a chunk's fixed cost is clearing, folding and writing w
+// counters), at most `chunks`.  Where that is more than one round of the CUs,
+// of the counts that fill one to four rounds the one with the least time --
+// rounds of items (0.31 ns per survivor, 0.2 ns per counter, 2 us), then the
+// reduction (0.4 ns per KB of slab).  1.5M survivors of 66 slices of 65,536
+// counters: the 15 chunks of the best fill took 180 us and 101 to reduce, the
+// fewer picked here take 143 and 67.
+// Every workgroup of the hashing evaluates this and all have to agree, so the
+// times are whole picoseconds (floating point may be contracted differently
+// from one compilation to the next); the reduction reads what the hashing
+// stored.
+constexpr int64_t kWideMinChunk = 16384;
+constexpr int kWideRange = 65536;   // counters of one hashing item at most
+constexpr int hash_chunks(int64_t n, int64_t chunks, int n_slices, int w, int n_cu) {
+  const int64_t need = (n + kWideMinChunk - 1) / kWideMinChunk;
+  const int most = (int)(need < 1 ? 1 : (need < chunks ? need : chunks));
+  const int items = n_slices * ((w + kWideRange - 1) / kWideRange);
+  if (most * items <= n_cu) return most;
+  const uint32_t n32 = n < 0xFFFFFFFFll ? (uint32_t)n : 0xFFFFFFFFu;
+  const int64_t fixed = 200ll * (w < kWideRange ? w : kWideRange) + 2000000;
+  int best = 1;
+  int64_t least = INT64_MAX;
+  for (int k = 1; k <= 4; ++k) {
+    const int fill = k * n_cu / items;
+    const int c = fill < 1 ? 1 : (fill < most ? fill : most);
+    const int rounds = (c * items + n_cu - 1) / n_cu;
+    const int64_t cost = rounds * (310ll * (n32 / (uint32_t)c) + fixed) +
+                         (int64_t)c * n_slices * w * 3 / 2;
+    if (cost < least) {
+      least = cost;
+      best = c;
+    }
+  }
+  return best;
+}
+
 // Counted build (tables without predicates): a key column's rows are
 // partitioned by key range, its distinct keys counted, and only those
 // hashed, each with its multiplicity as the weight.
