@@ -121,8 +121,11 @@ typedef struct {
  * Large tables without predicates whose non-negative keys repeat (fewer
  * values than rows) are counted first: each distinct key is then hashed
  * once, weighted with its multiplicity (the same counters; at most 4 GiB of
- * scratch more).  Keys are sampled and counted on the device in the same
- * call; a column they rule out is hashed row by row.  COMPASS_SERIAL=1 (a debugging mode,
+ * scratch more, and row by row where the device has no room for it).  Keys
+ * are sampled and counted on the device in the same call; a column they rule
+ * out is hashed row by row.  The environment's COMPASS_SCRATCH_BYTES stands
+ * in for such a device in tests: no pool grows beyond it.  COMPASS_SERIAL=1
+ * (a debugging mode,
  * read at each call) builds with one chunk per group of sketch rows and a
  * single compaction workgroup, so that no two workgroups combine partial
  * counters: its results equal the default launch's bit for bit. */

@@ -134,6 +134,7 @@ struct DeviceState {
   struct Scratch {
     void *p = nullptr;
     size_t bytes = 0;
+    size_t refused = ~(size_t)0;   // an extra of this size did not fit
   };
   std::map<hipStream_t, Scratch> scratch;
   static constexpr int kRing = 4;
@@ -166,6 +167,21 @@ static compass_status device_state(DeviceState **out) {
   return COMPASS_OK;
 }
 
+// Device memory for scratch, at most COMPASS_SCRATCH_BYTES of it (environment:
+// stands in for a device without room for more).
+static hipError_t scratch_alloc(void **p, size_t bytes) {
+  if (const char *e = getenv("COMPASS_SCRATCH_BYTES")) {
+    const long long v = atoll(e);
+    if (v > 0 && bytes > (size_t)v) return hipErrorOutOfMemory;
+  }
+  const hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess) {
+    *p = nullptr;
+    (void)hipGetLastError();
+  }
+  return e;
+}
+
 // Scratch of at least `bytes` for work on `stream` (grown, never shrunk,
 // until compass_release).  Growing waits for the device first: the old
 // buffer may still be in use by work already enqueued.
@@ -178,9 +194,43 @@ static compass_status ensure_scratch(DeviceState *ds, hipStream_t stream,
       HIP_OK(hipFree(sc.p));
       sc.p = nullptr;
     }
-    const size_t want = std::max(bytes, sc.bytes * 2);
+    size_t want = std::max(bytes, sc.bytes * 2);
     sc.bytes = 0;
-    HIP_OK(hipMalloc(&sc.p, want));
+    if (want > bytes && scratch_alloc(&sc.p, want) != hipSuccess) want = bytes;
+    if (!sc.p) HIP_OK(scratch_alloc(&sc.p, want));
+    sc.bytes = want;
+  }
+  *out = sc.p;
+  return COMPASS_OK;
+}
+
+// Scratch for a way of doing a call that takes more of it than the plain one:
+// `*out` is null where the device has no room (the buffer stays as it was, and
+// as much is not asked for again until compass_release) or a capture on
+// `stream` forbids to grow it.
+static compass_status extra_scratch(DeviceState *ds, hipStream_t stream,
+                                    size_t bytes, void **out) {
+  DeviceState::Scratch &sc = ds->scratch[stream];
+  *out = nullptr;
+  if (bytes > sc.bytes) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
+      (void)hipGetLastError();
+      return COMPASS_OK;
+    }
+    if (capture != hipStreamCaptureStatusNone || bytes >= sc.refused) return COMPASS_OK;
+    size_t want = std::max(bytes, sc.bytes * 2);
+    void *p = nullptr;
+    if (want > bytes && scratch_alloc(&p, want) != hipSuccess) want = bytes;
+    if (!p && scratch_alloc(&p, want) != hipSuccess) {
+      sc.refused = bytes;
+      return COMPASS_OK;
+    }
+    if (sc.p) {
+      HIP_OK(hipDeviceSynchronize());
+      HIP_OK(hipFree(sc.p));
+    }
+    sc.p = p;
     sc.bytes = want;
   }
   *out = sc.p;
@@ -860,16 +910,22 @@ static compass_status sketch_build_impl(
   CountedPlan cp;
   CountMap cp_map;
   memset(&cp_map, 0, sizeof cp_map);
-  const bool counted = !ar.fixed && !serial && !sink.out && n_preds == 0 &&
-                       plan_counted(base, n_sketches, d, n_rows, n_cu, cp);
-  const size_t count_bytes = counted ? cp.bytes : 0;
+  bool counted = !ar.fixed && !serial && !sink.out && n_preds == 0 &&
+                 plan_counted(base, n_sketches, d, n_rows, n_cu, cp);
   int64_t slab_rows = chunks;
-  if (counted)
+  void *scr = nullptr;
+  if (counted) {
     slab_rows = std::max<int64_t>(chunks, std::min<int64_t>(n_cu, slab_cap / slab_row));
-  void *scr;
-  st = ar.get(count_bytes + (size_t)slab_rows * slab_row, &scr);
-  if (st != COMPASS_OK) return st;
-  base.slab = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(scr) + count_bytes);
+    st = extra_scratch(ar.ds, stream, cp.bytes + (size_t)slab_rows * slab_row, &scr);
+    if (st != COMPASS_OK) return st;
+    counted = scr != nullptr;   // else the fused scan takes every row
+  }
+  if (!counted) {
+    st = ar.get((size_t)chunks * slab_row, &scr);
+    if (st != COMPASS_OK) return st;
+  }
+  base.slab = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(scr) +
+                                          (counted ? cp.bytes : 0));
   base.d = d;
   base.n_slices_total = S;
   if (counted) {
@@ -1675,15 +1731,8 @@ extern "C" compass_status compass_estimate(const compass_join_graph *g,
   std::vector<std::vector<NodeTask>> levels(max_level + 1);
   for (size_t k = 0; k < pl.tasks.size(); ++k)
     levels[pl.task_level[k]].push_back(pl.tasks[k]);
-  // a level is launched in groups of node tasks whose merge scratch
-  // (merged list + records per sketch row) stays within kNodeScratchBytes;
-  // groups run one after another on the stream and reuse the slots
   const int d = g->d, w = g->w;
-  const size_t per_task =
-      (size_t)d * std::max(1, pl.Lmax) * (sizeof(uint32_t) + sizeof(NodeRec));
-  const size_t group_tasks = std::min<size_t>(
-      kMaxGridZ, std::max<size_t>(1, kNodeScratchBytes / per_task));
-  size_t max_level_tasks = 0;
+  size_t level_most = 0;
   std::vector<NodeTask> flat;
   std::vector<size_t> level_off;
   // within a level: one-child nodes, other nodes, triangle apexes, so that
@@ -1696,11 +1745,9 @@ extern "C" compass_status compass_estimate(const compass_join_graph *g,
                      [&](const NodeTask &a, const NodeTask &b) {
                        return kind(a) < kind(b);
                      });
-    for (size_t k = 0; k < lv.size(); ++k)
-      lv[k].scratch_slot = (int)(k % group_tasks);
     level_off.push_back(flat.size());
     flat.insert(flat.end(), lv.begin(), lv.end());
-    max_level_tasks = std::max(max_level_tasks, std::min(lv.size(), group_tasks));
+    level_most = std::max(level_most, lv.size());
   }
   // scratch layout
   size_t off = 0;
@@ -1741,10 +1788,6 @@ extern "C" compass_status compass_estimate(const compass_join_graph *g,
   const size_t o_sorted = carve(sizeof(uint64_t) * 2 * g->n_edges * d * (size_t)w);
   const size_t o_msg = carve(16ull * pl.n_msg_slots * d * (size_t)w);
   const size_t o_fmsg = carve(8ull * pl.n_fmsg_slots * d * (size_t)w);
-  const size_t o_merged = carve(4ull * max_level_tasks * d * (size_t)std::max(1, pl.Lmax));
-  const size_t o_nrec = carve(sizeof(NodeRec) * max_level_tasks * d *
-                              (size_t)std::max(1, pl.Lmax));
-  const size_t o_n1tot = carve(16ull * 2 * kN1MaxChunks * max_level_tasks * d);
   const size_t o_xout = carve(16ull * std::max(1, pl.n_x_slots) * d);
   const size_t np = std::max(1, pl.n_prep_slots);
   const size_t lp = std::max(1, pl.Lprep);
@@ -1763,9 +1806,35 @@ extern "C" compass_status compass_estimate(const compass_join_graph *g,
   const size_t o_glists = carve(4ull * std::max<int64_t>(1, pl.glists_len));
   const size_t o_gmsg = carve(16ull * std::max<int64_t>(1, pl.gmsg_len));
   const size_t o_approx = carve(8ull * std::max(1, pl.n_approx_slots) * d);
-  void *scratch;
-  st = ensure_scratch(ds, stream, off, &scratch);
-  if (st != COMPASS_OK) return st;
+  // a level is launched in groups of node tasks whose merge scratch (merged
+  // list + records per sketch row) stays within kNodeScratchBytes, or within
+  // what the device has room for; groups run one after another on the stream
+  // and reuse the slots
+  const size_t per_task =
+      (size_t)d * std::max(1, pl.Lmax) * (sizeof(uint32_t) + sizeof(NodeRec));
+  size_t group_tasks = std::min<size_t>(
+      kMaxGridZ, std::max<size_t>(1, kNodeScratchBytes / per_task));
+  group_tasks = std::min(group_tasks, std::max<size_t>(1, level_most));
+  size_t o_merged, o_nrec, o_n1tot;
+  const size_t off_nodes = off;
+  void *scratch = nullptr;
+  for (bool first = true; !scratch; first = false) {
+    off = off_nodes;
+    o_merged = carve(4ull * group_tasks * d * (size_t)std::max(1, pl.Lmax));
+    o_nrec = carve(sizeof(NodeRec) * group_tasks * d * (size_t)std::max(1, pl.Lmax));
+    o_n1tot = carve(16ull * 2 * kN1MaxChunks * group_tasks * d);
+    st = first && group_tasks > 1 ? extra_scratch(ds, stream, off, &scratch)
+                                  : ensure_scratch(ds, stream, off, &scratch);
+    if (st != COMPASS_OK && group_tasks == 1) return st;
+    if (!scratch || st != COMPASS_OK) {
+      scratch = nullptr;
+      g_err.clear();
+      group_tasks = (group_tasks + 1) / 2;
+    }
+  }
+  for (size_t lv = 0; lv < levels.size(); ++lv)
+    for (size_t k = 0; k < levels[lv].size(); ++k)
+      flat[level_off[lv] + k].scratch_slot = (int)(k % group_tasks);
   char *base = reinterpret_cast<char *>(scratch);
 
   // one staging upload of every host-built table
@@ -2497,14 +2566,15 @@ extern "C" compass_status compass_agms_build(
       total += align256((size_t)T.cap[c] * T.n_groups * sizeof(uint4));
     }
   }
-  st = ensure_scratch(ds, stream, total, &scr);
-  if (st != COMPASS_OK && T.n_cols > 0) {   // no room for the sign tables
-    (void)hipGetLastError();
-    g_err.clear();
-    memset(&T, 0, sizeof T);
-    st = ensure_scratch(ds, stream, align256(bytes), &scr);
+  if (T.n_cols > 0) {
+    st = extra_scratch(ds, stream, total, &scr);
+    if (st != COMPASS_OK) return st;
+    if (!scr) memset(&T, 0, sizeof T);   // no room for the sign tables
   }
-  if (st != COMPASS_OK) return st;
+  if (T.n_cols == 0) {
+    st = ensure_scratch(ds, stream, align256(bytes), &scr);
+    if (st != COMPASS_OK) return st;
+  }
   st = upload(ds, scr, sd.data(), bytes, stream);
   if (st != COMPASS_OK) return st;
   if (T.n_cols > 0) {
