@@ -870,6 +870,7 @@ static compass_status sketch_build_impl(
   // writing the group's counters; 3 us) and of the slab's reduction.  0.2M
   // and 1.6M rows of 15 slices of 3000 counters: 189 and 188 us at eight
   // tiles, 43 us each on average this way; 2000 rows of 7 slices: 34 and 13.
+  const int64_t plain_chunks = chunks;
   if (chunks * n_groups_total < n_cu && !serial) {
     const double per_ns = base.bm.pow2 ? 2.4 : 1.2;
     double least = 0;
@@ -900,11 +901,13 @@ static compass_status sketch_build_impl(
   if (slab_row > slab_cap)
     return fail(COMPASS_E_RANGE, "one chunk's partial counters (%zu bytes) "
                 "exceed the scratch", slab_row);
-  chunks = std::min<int64_t>(chunks, std::max<size_t>(1, slab_cap / slab_row));
-  if (serial) chunks = 1;
-  const int64_t rows_per_chunk = fused_rows_per_chunk(n_rows, chunks, kScanTile);
-  chunks = (n_rows + rows_per_chunk - 1) / rows_per_chunk;
-  base.rows_per_chunk = rows_per_chunk;
+  auto cut = [&](int64_t c) {
+    c = std::min<int64_t>(c, std::max<size_t>(1, slab_cap / slab_row));
+    if (serial) c = 1;
+    base.rows_per_chunk = fused_rows_per_chunk(n_rows, c, kScanTile);
+    chunks = (n_rows + base.rows_per_chunk - 1) / base.rows_per_chunk;
+  };
+  cut(chunks);
   // key columns with few distinct keys for their rows are counted first and
   // hashed once per key; the fused scan takes what the counting leaves
   CountedPlan cp;
@@ -920,7 +923,12 @@ static compass_status sketch_build_impl(
     if (st != COMPASS_OK) return st;
     counted = scr != nullptr;   // else the fused scan takes every row
   }
-  if (!counted) {
+  if (!counted && !ar.fixed && chunks > plain_chunks) {
+    st = extra_scratch(ar.ds, stream, (size_t)chunks * slab_row, &scr);
+    if (st != COMPASS_OK) return st;
+    if (!scr) cut(plain_chunks);
+  }
+  if (!scr) {
     st = ar.get((size_t)chunks * slab_row, &scr);
     if (st != COMPASS_OK) return st;
   }

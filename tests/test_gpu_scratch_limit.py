@@ -95,6 +95,30 @@ def test_pool_grows_to_what_is_needed():
 
 
 @gpu
+def test_small_table_without_room(oracle):
+    """A table spread over more chunks than its tiles need, and over as few as
+    fit."""
+    torch = _torch()
+    from paper_2102_02440_amd import compass as C
+    rng = np.random.default_rng(8)
+    n, d, w = 130_001, 3, 16384
+    col = rng.integers(0, n, n).astype(np.int32)
+    key = torch.from_numpy(col).cuda()
+    seeds = [W.draw_seeds(rng, 1, d)[0]]
+    n_o, ref = oracle.build_table_sketches(W.Table("t", {"k": col}), ["k"], seeds, d, w)
+    # slab rows of 3 x 16384 int32: the plain chunks alone, and all
+    for chunks in (2, 3, 64):
+        print("[case] small table, slab rows", chunks, flush=True)
+        with _limit(C, chunks * d * w * 4):
+            cnt = [torch.full((d, w), 3, dtype=torch.int32, device="cuda")]
+            ns = torch.zeros(1, dtype=torch.int64, device="cuda")
+            C.sketch_build(n, [], [], [key], seeds, cnt, ns, d, w, 32)
+            torch.cuda.synchronize()
+        assert ns.item() == n == n_o
+        assert np.array_equal(cnt[0].cpu().numpy(), ref[0])
+
+
+@gpu
 def test_agms_build_without_room(oracle):
     torch = _torch()
     from paper_2102_02440_amd import compass as C
