@@ -522,6 +522,7 @@ struct CountedPlan {
   CountArgs a;
   CountTiles tiles;
   CountMap map;
+  int all_of[kMaxSketches];        // distinct key column of every sketch
   int max_bins = 0, max_items = 0, max_stride = 0;
   size_t o_sg = 0, sg_bytes = 0;   // super-group totals: cleared first
   size_t o_chunks = 0, bytes = 0;
@@ -565,7 +566,10 @@ static bool plan_counted(const BuildParams &base, int n_sketches, int d,
     counted[c] = (int8_t)A.n_cols++;
   }
   if (A.n_cols == 0) return false;
-  for (int s = 0; s < n_sketches; ++s) cp.map.col[s] = counted[all_of[s]];
+  for (int s = 0; s < n_sketches; ++s) {
+    cp.map.col[s] = counted[all_of[s]];
+    cp.all_of[s] = all_of[s];
+  }
   cp.tiles = count_tiles(n_rows, A.n_cols, 2 * n_cu);
   A.n_rows = n_rows;
   A.n_selected = base.n_selected;
@@ -650,7 +654,7 @@ static compass_status run_counted(const CountedPlan &cp, int32_t *slab, int max_
   WeightedArgs W;
   memset(&W, 0, sizeof W);
   W.st = A.st;
-  W.slice_chunks = const_cast<int32_t *>(cp.map.slice_chunks);
+  W.slice_chunks = cp.map.slice_chunks;
   W.slab = slab;
   W.n_slices_total = n_sketches * d;
   W.max_chunks = max_chunks;
@@ -950,6 +954,7 @@ static compass_status sketch_build_impl(
     st = run_counted(cp, base.slab, (int)slab_rows, sketches, n_sketches, d, base.bm,
                      n_cu, stream);
     if (st != COMPASS_OK) return st;
+    cp.map.max_chunks = (int32_t)slab_rows;
     base.cmap = cp_map = cp.map;
   }
 
@@ -962,7 +967,15 @@ static compass_status sketch_build_impl(
     P.slice_base = slice;
     P.group_begin[0] = 0;
     while (slice < S && ng < kMaxLaunchGroups) {
-      const int gs = std::min(per_group, S - slice);
+      int gs = std::min(per_group, S - slice);
+      if (counted) {   // the slices of one column, in equal shares
+        int run = d - slice % d;
+        for (int s = slice / d + 1;
+             s < n_sketches && cp.all_of[s] == cp.all_of[slice / d]; ++s)
+          run += d;
+        const int groups = live_groups(run, per_max, tiles, n_cu);
+        gs = (run + groups - 1) / groups;
+      }
       if (ls + gs > kMaxLaunchSlices) break;
       for (int q = 0; q < gs; ++q) {
         const int gsl = slice + q;
@@ -982,9 +995,13 @@ static compass_status sketch_build_impl(
     for (int g = 0; g < ng; ++g)
       max_group = std::max(max_group, P.group_begin[g + 1] - P.group_begin[g]);
     const size_t lds = (size_t)max_group * w * 4 + queue_bytes;
-    const int64_t blocks = chunks * ng;
+    int64_t blocks = chunks * ng;
     if (blocks > 0x7FFFFFF0)
       return fail(COMPASS_E_RANGE, "too many workgroups");
+    if (counted) {   // the device shares them out
+      blocks = std::max(2 * n_cu, kMaxLaunchSlices);
+      P.n_cu = (int32_t)blocks / 2;
+    }
     P.n_blocks = (int32_t)blocks;
     ProfScope ps("scan_sketch", stream);
     HIP_OK(launch_scan_sketch(P, (int)blocks, lds, stream));

@@ -82,7 +82,8 @@ struct CountState {
 // column (an index into `st`, -1: not counted) is not bad.
 struct CountMap {
   const CountState *st;          // nullptr: nothing is counted
-  const int32_t *slice_chunks;   // slab rows of a counted slice
+  int32_t *slice_chunks;         // slab rows written of every slice
+  int32_t max_chunks;            // slab rows there are
   int8_t col[kMaxSketches];
   __device__ bool counted(int s) const {
     return st && col[s] >= 0 && !st[col[s]].bad;
@@ -101,7 +102,7 @@ struct BuildParams {
   int32_t d;
   int32_t n_slices_total;  // n_sketches * d of the call (slab row count)
   int32_t n_blocks;     // (chunk, slice group) pairs of a fused-scan launch
-  int32_t pad_nb;
+  int32_t n_cu;         // a counted build's launch: compute units
   BucketMod bm;
   BucketMod bm1;        // first dimension of a partitioned sketch (w1)
   PredDev preds[kMaxPreds];

@@ -150,27 +150,46 @@ constexpr int kCntMaxSg = 64;
 
 // The key range [0, range) within which a column of n_rows keys hashed into
 // `slices` sketch rows is counted, in bins of kCntBinKeys; 0 bins: not at
-// all.  The range bounds the distinct keys (at most one per value), so it
-// is what the choice guarantees: hashing every row costs n_rows * slices
-// updates, the counted build at most range * slices of them plus the
-// partition and counting passes, which cost about as much as kCntRowCost
-// updates per row: 3.3 ns per 1000 rows of a column against 1.6 ns per 1000
-// updates is 2.1, taken with a margin for clustered keys and narrow tables.
-// Below kCntMinUpdates the seven launches eat the gain: 63M updates of 4.5M
-// rows take 108 us counted and 146 us hashed row by row.  Where another
-// column of the table pays for them, kCntAlsoUpdates is enough
-// (7 sketch rows of 4.5M keys beside 14 of another column: 145 us hashed row
-// by row, 35 counted).
+// all.  The range bounds the distinct keys of a column that fits it (at most
+// one per value): hashing every row costs n_rows * slices updates, the
+// counted build at most range * slices of them plus the partition and
+// counting passes, which cost about as much as kCntRowCost updates per row:
+// 3.3 ns per 1000 rows of a column against 1.6 ns per 1000 updates is 2.1,
+// taken with a margin for clustered keys and narrow tables.
+// The host does not know which columns fit.  One that does not (a primary
+// key, keys that hardly repeat) is found out by a sample on the device and
+// hashed row by row, but pays for five launches without work, some 17 us:
+// 3 % at 5e8 updates, 6 to 12 at 2e8, up to 22 at 8e7 (140 -> 170 us); one
+// that the sample lets pass and that overflows the list of outside keys pays
+// the partition as well (4.3M rows, 190 -> 290 us).  Columns that fit gain
+// from about 5e7 updates on (7 sketch rows, keys repeated 20 times: 113 ->
+// 85 us at 5e7, 320 -> 158 at 2e8; 4 times: 113 -> 105 and 318 -> 229), with
+// few sketch rows later (5 rows, 20 times: 104 -> 101 us at 5e7, 152 -> 107
+// at 8e7): the updates saved have to pay too.  Where another column of the
+// table pays for the launches, kCntAlsoUpdates is enough (2e7 beside the
+// first column's 3 sketches: 133 -> 101 us repeated 10 times, 133 -> 130 if it
+// does not fit; the least gain is at 1.5e7, 133 -> 98 and 133 -> 136).
 constexpr double kCntRowCost = 3.5;
 constexpr double kCntMinUpdates = 5.0e7;   // below: launches would not pay
+constexpr double kCntMinSaved = 2.0e7;     // updates beyond the rows' own cost
 constexpr double kCntAlsoUpdates = 1.5e7;
 inline int counted_bins(int64_t n_rows, int slices, bool also = false) {
   if (n_rows >= ((int64_t)1 << 31) - kCntTile) return 0;  // int32 weights
   if ((double)n_rows * slices < (also ? kCntAlsoUpdates : kCntMinUpdates)) return 0;
+  if (!also && (double)n_rows * (slices - kCntRowCost) < kCntMinSaved) return 0;
   const double share = 0.9 - kCntRowCost / slices;
   if (share <= 0) return 0;
   const double bins = (double)n_rows * share / kCntBinKeys;
   return (int)std::min<double>(bins, kCntMaxBins);
+}
+
+// Slice groups of a run of one column's slices in a counted build's scan: as
+// few as the LDS allows (per_max slices each), but enough of them for a
+// workgroup per compute unit where the column alone is left to the scan.
+constexpr int live_groups(int run, int per_max, int64_t tiles, int cus) {
+  const int64_t fill = (cus + tiles - 1) / tiles;
+  const int least = (run + per_max - 1) / per_max;
+  return least > fill ? least : (int)(fill < run ? fill : run);
 }
 
 // A workgroup's decision on a word that other workgroups of the same launch
@@ -183,6 +202,81 @@ constexpr bool block_reads(uint32_t *shared, bool reader, Load load, Barrier bar
   if (reader) *shared = load();
   barrier();
   return *shared != 0;
+}
+
+// Workgroups are dealt to the dies round-robin; pieces of work are numbered die
+// by die, so that neighbours run on one die and share its L2.  The piece of
+// workgroup `block`, -1: none (the last die's share is not full).
+constexpr int32_t piece_by_die(uint32_t block, uint32_t pieces, uint32_t dies) {
+  const uint32_t per_die = (pieces + dies - 1) / dies, at = block / dies;
+  const uint32_t piece = block % dies * per_die + at;
+  return at < per_die && piece < pieces ? (int32_t)piece : -1;
+}
+
+// The workgroups of a counted build's scan, which takes the slice groups whose
+// columns are not counted ("live", known on the device only): one per compute
+// unit, or two where that leaves each eight tiles, shared out to the live
+// groups in proportion to their slices, each group's rows cut into that many
+// chunks of whole tiles, at most max_chunks.  Groups of one size keep the
+// plain scan's numbering (the groups of a chunk in a row, to read its keys
+// through one L2).  (constexpr: callable on the host and on the device.)
+struct LiveSplit {
+  int32_t group, chunk, chunks;   // group -1: the workgroup has no work
+  uint32_t chunk_tiles;
+};
+struct LiveChunks {
+  uint32_t chunks, tiles;   // chunks of a group, tiles of a chunk
+};
+constexpr LiveChunks live_chunks(uint32_t blocks, uint32_t share, uint32_t of, uint32_t tiles,
+                                 uint32_t max_chunks) {
+  uint32_t c = blocks * share / of;
+  c = c < max_chunks ? c : max_chunks;
+  c = c < tiles ? c : tiles;
+  c = c > 1 ? c : 1;
+  const uint32_t per = (tiles + c - 1) / c;
+  return LiveChunks{(tiles + per - 1) / per, per};
+}
+constexpr LiveSplit live_split(const int32_t *group_begin, int n_groups, uint32_t live,
+                               uint32_t block, uint32_t dies, uint32_t cus, uint32_t tiles,
+                               uint32_t max_chunks) {
+  const LiveSplit none{-1, 0, 0, 0};
+  uint32_t slices = 0, size = 0, n_live = 0;
+  bool equal = true;
+  for (int g = 0; g < n_groups; ++g) {
+    if (!((live >> g) & 1u)) continue;
+    const uint32_t ns = (uint32_t)(group_begin[g + 1] - group_begin[g]);
+    equal = equal && (n_live == 0 || ns == size);
+    size = ns;
+    slices += ns;
+    ++n_live;
+  }
+  if (n_live == 0) return none;
+  const uint32_t blocks = tiles * n_live >= 16 * cus ? 2 * cus : cus;
+  LiveChunks c = live_chunks(blocks, size, slices, tiles, max_chunks);
+  uint32_t used = n_live * c.chunks;
+  if (!equal) {
+    used = 0;
+    for (int g = 0; g < n_groups; ++g)
+      if ((live >> g) & 1u)
+        used += live_chunks(blocks, (uint32_t)(group_begin[g + 1] - group_begin[g]), slices,
+                            tiles, max_chunks).chunks;
+  }
+  const int32_t piece = piece_by_die(block, used, dies);
+  if (piece < 0) return none;
+  uint32_t at = equal ? (uint32_t)piece % n_live : (uint32_t)piece;
+  for (int g = 0; g < n_groups; ++g) {
+    if (!((live >> g) & 1u)) continue;
+    if (equal) {
+      if (at-- == 0)
+        return LiveSplit{g, (int32_t)((uint32_t)piece / n_live), (int32_t)c.chunks, c.tiles};
+      continue;
+    }
+    c = live_chunks(blocks, (uint32_t)(group_begin[g + 1] - group_begin[g]), slices, tiles,
+                    max_chunks);
+    if (at < c.chunks) return LiveSplit{g, (int32_t)at, (int32_t)c.chunks, c.tiles};
+    at -= c.chunks;
+  }
+  return none;
 }
 
 // Tiles of a partitioned column: workgroups of tiles_per_wg tiles each,

@@ -27,7 +27,7 @@
 // 112 + plan 9 + items 91 + emit 29 + weighted scan 76 (6.0M distinct keys)
 // + the empty scan 5 + reduction 8.  Uniform keys (4 per value, 14 sketch
 // rows) 887 -> 477 us.  A table whose columns turn out bad pays the five
-// empty launches, 12 us.
+// empty launches, 17 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

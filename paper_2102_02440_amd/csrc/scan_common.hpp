@@ -207,14 +207,12 @@ __device__ int compact_tile(const J &job, int64_t base, int nt, int n_preds,
 // slices [sb, se) (slice sl at cnt + (sl - sb) * w), in tiles of
 // kBuildThreads * kRowsPerThread rows.  Returns, in thread 0, the number of
 // qualifying rows.  `queue` holds a tile's row offsets (unused, and may be
-// null, when the job has no predicates); `s_qn` is a shared counter.  With
-// kSome only the slices whose bit sl - sb of `live` is set are hashed (groups
-// of at most 64).  Every thread of the block must call it.
-template <class J, int kRowsPerThread = kBuildRowsPerThread, bool kSome = false>
+// null, when the job has no predicates); `s_qn` is a shared counter.  Every
+// thread of the block must call it.
+template <class J, int kRowsPerThread = kBuildRowsPerThread>
 __device__ uint64_t scan_rows(const J &job, int64_t row0, int64_t row1,
                               int sb, int se, int32_t *cnt, int32_t *queue,
-                              int32_t *s_qn, RowSink sink = RowSink{},
-                              uint64_t live = 0) {
+                              int32_t *s_qn, RowSink sink = RowSink{}) {
   __shared__ unsigned long long s_roff;
   constexpr int kTile = kBuildThreads * kRowsPerThread;
   // the slice range is the same in every lane: say so, so that the slice
@@ -299,7 +297,6 @@ __device__ uint64_t scan_rows(const J &job, int64_t row0, int64_t row1,
     }
     for (int sl0 = sb; sl0 < se; ++sl0) {
       const int sl = __builtin_amdgcn_readfirstlane(sl0);
-      if (kSome && !((live >> (sl - sb)) & 1ull)) continue;
       const int s = job.slice_sketch(sl);
       if (s != cur_sketch) {
         cur_sketch = s;
