@@ -2024,14 +2024,30 @@ static int bin2d_shift(int d, int w1, int w2) {
   return rs;
 }
 
-// The segmented build, in the same batches.  Up to kSegMaxBins tiles per
-// sketch row a chunk of 8192 rows has 32 records or more of each, a 64-byte
-// piece.  From kSegMinRows rows on: a chunk is twice the binned build's tile,
-// so few rows leave it fewer workgroups.  d = 5, 1024 x 1024 counters: 39 us
-// binned and 60 segmented at 100,000 rows, 75 and 71 at 1M, 511 and 280 at
-// 10M (55 and 68, 231 and 109 with a tenth of the rows selected); 2048 x 2048
-// (kSegMaxBins tiles): 90 and 89 at 1M, 834 and 271 at 10M.
-constexpr int64_t kSegMinRows = (int64_t)1 << 21;
+// Rows of a batch from which on the segmented build takes it.  Up to
+// kSegMaxBins tiles per sketch row a chunk of 8192 rows has 32 records or more
+// of each, a 64-byte piece.  But a chunk is twice the binned build's tile: few
+// rows leave it fewer workgroups, and rows just past a multiple of a chunk per
+// CU a last round half idle; and where four joins' keys are 64-bit columns and
+// wide, the scan reloads them for want of registers.  Binned and segmented,
+// us, d = 5, all rows selected (half of them: from 3M rows on the segmented
+// build takes 0.6 to 0.8 of the binned one's time in every shape below):
+//   1024 x 1024      2.1M rows 128, 142   3M 180, 149   5M 250, 195   30M 1514, 707
+//     64-bit keys              197, 230      276, 240      393, 334       2211, 1415
+//   128 x 128 x 128            166, 161      235, 193      334, 247       2238, 934
+//     64-bit keys              257, 301      357, 332      540, 464       3153, 2039
+//   32 x 32 x 32 x 32          183, 243      256, 274      363, 370       1991, 1365
+//     64-bit keys              295, 448      406, 479      600, 684       3122, 2947
+//   the same at                8.4M 539, 464   8.5M 632, 518   12M 826, 620
+//     64-bit keys                   859, 911       1023, 1064      1277, 1264
+static int64_t seg_min_rows(const BuildParams &P, int kd) {
+  if (kd < 4) return (int64_t)3 << 20;
+  bool wide = false;
+  for (int k = 0; k < kd; ++k) wide = wide || P.keys[k].dtype == kDtI64;
+  return (int64_t)(wide ? 12 : 8) << 20;
+}
+
+// The segmented build, in the batches of the binned one.
 static compass_status sketch_build_2d_segments(const BuildParams &P,
                                                const KdDims &kx,
                                                DeviceState *ds, int64_t n_rows,
@@ -2086,7 +2102,7 @@ static compass_status sketch_build_2d_segments(const BuildParams &P,
     a.block_chunks = (int32_t)((a.rows_per_block + kSegChunk - 1) / kSegChunk);
     a.row0 = b0;
     a.row1 = b1;
-    ProfScope ps("scan2d", stream);
+    ProfScope ps("scan2d", stream), seg("scan2d_segments", stream);
     HIP_OK(launch_fill_zero(a.bin_total, (int64_t)align256((size_t)(a.n_bins + 1) * 4),
                             stream));
     HIP_OK(launch_scan2d_segments(P, a, kx, (accumulate || b0 > 0) ? 1 : 0, ds->n_cu,
@@ -2113,7 +2129,7 @@ static compass_status sketch_build_2d_binned(const BuildParams &P,
       kBuildTile, budget / (4 * (int64_t)d) / kBuildTile * kBuildTile);
   const int nbr = (w1 + (1 << r_shift) - 1) >> r_shift;
   if (nbr <= kSegMaxBins && d * nbr <= kSegMaxTotal &&
-      std::min(n_rows, batch) >= kSegMinRows)
+      std::min(n_rows, batch) >= seg_min_rows(P, kx.kd))
     return sketch_build_2d_segments(P, kx, ds, n_rows, batch, d, w1, w2, r_shift,
                                     accumulate, stream);
   Bin2dArgs a;
