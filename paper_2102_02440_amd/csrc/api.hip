@@ -2026,22 +2026,21 @@ static int bin2d_shift(int d, int w1, int w2) {
 
 // Rows of a batch from which on the segmented build takes it.  Up to
 // kSegMaxBins tiles per sketch row a chunk of 8192 rows has 32 records or more
-// of each, a 64-byte piece.  But a chunk is twice the binned build's tile: few
-// rows leave it fewer workgroups, and rows just past a multiple of a chunk per
-// CU a last round half idle; and where four joins' keys are 64-bit columns and
-// wide, the scan reloads them for want of registers.  Binned and segmented,
-// us, d = 5, all rows selected (half of them: from 3M rows on the segmented
-// build takes 0.6 to 0.8 of the binned one's time in every shape below):
-//   1024 x 1024      2.1M rows 128, 142   3M 180, 149   5M 250, 195   30M 1514, 707
-//     64-bit keys              197, 230      276, 240      393, 334       2211, 1415
-//   128 x 128 x 128            166, 161      235, 193      334, 247       2238, 934
-//     64-bit keys              257, 301      357, 332      540, 464       3153, 2039
-//   32 x 32 x 32 x 32          183, 243      256, 274      363, 370       1991, 1365
-//     64-bit keys              295, 448      406, 479      600, 684       3122, 2947
-//   the same at                8.4M 539, 464   8.5M 632, 518   12M 826, 620
-//     64-bit keys                   859, 911       1023, 1064      1277, 1264
+// of each, a 64-byte piece.  But a chunk is twice the binned build's tile (few
+// rows leave it fewer workgroups: 39 us binned and 60 segmented at 100,000
+// rows), and four joins take more registers than there are, above all with
+// wide keys of 64-bit columns.  Binned and segmented, us, d = 5, every row
+// selected (of half the rows the segmented build takes less by more):
+//   1024 x 1024, 2^21 rows 132, 119   2^21 + 1 124, 128   3M 179, 137   30M 1514, 707
+//     64-bit keys          181, 167            197, 199      274, 208       2211, 1415
+//   128 x 128 x 128        159, 120            164, 144      234, 176       2238, 934
+//     64-bit keys          223, 196            258, 252      360, 285       3153, 2039
+//   32 x 32 x 32 x 32      167, 193            183, 243      256, 274       1991, 1365
+//     64-bit keys          241, 302            295, 448      406, 479       3122, 2947
+//   the same at       8.4M 539, 464       8.5M 632, 518       12M 826, 620
+//     64-bit keys          859, 911           1023, 1064         1277, 1264
 static int64_t seg_min_rows(const BuildParams &P, int kd) {
-  if (kd < 4) return (int64_t)3 << 20;
+  if (kd < 4) return (int64_t)1 << 21;
   bool wide = false;
   for (int k = 0; k < kd; ++k) wide = wide || P.keys[k].dtype == kDtI64;
   return (int64_t)(wide ? 12 : 8) << 20;

@@ -589,11 +589,17 @@ __global__ __launch_bounds__(kBuildThreads) void seg_scan_kernel(
       const int64_t chunk = (int64_t)blockIdx.x * a.block_chunks + used++;
       for (int i = 0; i < d; ++i) {
         uint32_t rec[R];      // tile << 16 | record
+#pragma unroll
+        for (int k = R / 2; k < R; ++k) rec[k] = 0;
         uint32_t rank[R];
         seg_records<0, KD>(P, a, kx, rows, i, wide, pow2, x, rec);
         // (apart: interleaved, the two halves' values do not fit the registers)
         __builtin_amdgcn_sched_barrier(0);
-        seg_records<4, KD>(P, a, kx, rows, i, wide, pow2, x, rec);
+        // (no lane has rows of that half else; uniform.  1024 x 1024 counters,
+        // a chunk and a half per CU: 143 -> 128 us.  Four joins would spill
+        // more registers for the branch than it saves.)
+        if (KD == 4 || n > kChunk / 2)
+          seg_records<4, KD>(P, a, kx, rows, i, wide, pow2, x, rec);
 #pragma unroll
         for (int k = 0; k < R; ++k)
           rank[k] = (int)threadIdx.x + k * kBuildThreads < n

@@ -57,13 +57,15 @@ def _build(C, torch, n, cols, preds, keys, seeds, d, widths, bits, budget):
 
 @gpu
 @pytest.mark.parametrize("widths,d,bits,n,hi,keys_are", [
-    ([512, 512], 3, 32, 3 * M, None, "zipf"),        # whole chunks, one heavy tile
-    ([255, 16384], 2, 32, 3 * M + 4097, 64, "zipf"),  # one matrix row to a tile
-    ([64, 50, 20], 3, 64, 3 * M + 1, 64, "wide"),     # widths not powers of two
+    ([512, 512], 3, 32, 2 * M, None, "zipf"),        # whole chunks, one heavy tile
+    ([512, 512], 3, 32, 2 * M + 1, None, "zipf"),    # a chunk and a half per block
+    ([255, 16384], 2, 32, 2 * M + 4097, 64, "zipf"),  # one matrix row to a tile
+    ([64, 50, 20], 3, 64, 2 * M + 1, 64, "wide"),     # widths not powers of two
+    ([64, 50, 20], 3, 64, 3 * M + 4095, None, "wide"),
     ([16, 16, 16, 16], 2, 32, 8 * M + 1, None, "zipf"),
     ([13, 11, 9, 7], 3, 64, 12 * M + 5, 30, "wide"),
-    ([7, 3], 5, 64, 3 * M + 9, 64, "one"),            # every row in one counter
-    ([300, 100], 2, 32, 3 * M + 9, -1, "zipf"),       # no row selected
+    ([7, 3], 5, 64, 2 * M + 9, 64, "one"),            # every row in one counter
+    ([300, 100], 2, 32, 2 * M + 9, -1, "zipf"),       # no row selected
 ])
 def test_segments(widths, d, bits, n, hi, keys_are):
     torch = _torch()
@@ -92,7 +94,7 @@ def test_segments_in_batches(hi, bits):
     torch = _torch()
     from paper_2102_02440_amd import compass as C
     d, widths = 3, [200, 150]
-    n = 2 * 3 * M + 100_003
+    n = 2 * 2 * M + 100_003
     print("[case] segments in batches", hi, bits, n, flush=True)
     rng = np.random.default_rng(bits + (hi or 0))
     keys = _keys(torch, rng, n, 2, "zipf")
@@ -100,7 +102,7 @@ def test_segments_in_batches(hi, bits):
     preds = [] if hi is None else [{"col": 0, "kind": "range", "lo": 0, "hi": hi}]
     seeds = list(W.draw_seeds(rng, 2, d))
     args = (C, torch, n, [attr] if preds else [], preds, keys, seeds, d, widths, bits)
-    got, ns, launches = _build(*args, 4 * d * 3 * M)
+    got, ns, launches = _build(*args, 4 * d * 2 * M)
     whole, nw, one = _build(*args, None)
     ref, nr, none = _build(*args, 4 * d * M)
     assert (launches, one, none) == (6, 2, 0)
@@ -110,7 +112,7 @@ def test_segments_in_batches(hi, bits):
 
 @gpu
 @pytest.mark.parametrize("widths,n,dtype,segments", [
-    ([64, 64], 3 * M - 1, 32, 0), ([64, 64], 3 * M, 64, 1),
+    ([64, 64], 2 * M - 1, 32, 0), ([64, 64], 2 * M, 64, 1),
     ([8, 8, 8, 8], 8 * M - 1, 32, 0), ([8, 8, 8, 8], 8 * M, 32, 1),
     ([8, 8, 8, 8], 8 * M, 64, 0), ([8, 8, 8, 8], 12 * M, 64, 1),
 ])
