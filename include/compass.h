@@ -587,9 +587,11 @@ compass_status compass_enumerate_greedy(int32_t n_tables, int32_t n_edges,
 /* Kernel timing for measurement: while enabled, the library records a pair
  * of HIP events on the launch stream around each kernel launch it makes.
  * compass_profile_take(name) waits for the recorded events of kernel `name`
- * ("scan_sketch", "count", "weighted_scan", "slab_reduce", "wide_compact", "wide_hash", "fill_zero",
- * "sort_rows", "node", "tri_order", "tri_lane", "finish", "scan2d", within it
- * "scan2d_segments" where the build is segmented, "chain3", "agms_build", "agms_estimate", "generic"),
+ * ("scan_sketch", "count", "weighted_scan", "slab_reduce", "wide_compact",
+ * "wide_hash", "fill_zero", "sort_rows", "node", "tri_order", "tri_lane",
+ * "finish", "scan2d", "chain3", "agms_build", "agms_estimate", "generic"; and
+ * which way a build went, within those: "scan2d_segments", "agms_signs" with
+ * sign tables, "agms_direct" without),
  * returns their count and summed elapsed milliseconds, and forgets them.
  * compass_profile_select(names) restricts the recording to the kernels in
  * the comma-separated list `names` (NULL or "": every kernel), so that a

@@ -2646,7 +2646,7 @@ extern "C" compass_status compass_agms_build(
   const int64_t blocks = std::min<int64_t>(tiles, 4ll * ds->n_cu);
   P.rows_per_chunk = (tiles + blocks - 1) / blocks * P.tile;
   const int64_t chunks = (n_rows + P.rows_per_chunk - 1) / P.rows_per_chunk;
-  ProfScope ps("agms_build", stream);
+  ProfScope ps("agms_build", stream), tab(P.tab.st ? "agms_signs" : "agms_direct", stream);
   HIP_OK(launch_agms_build(P, (int)chunks, ds->n_cu, stream));
   return COMPASS_OK;
 }
