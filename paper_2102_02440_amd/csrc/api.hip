@@ -2631,16 +2631,23 @@ extern "C" compass_status compass_agms_build(
   if (n_rows == 0) return COMPASS_OK;
   // A workgroup of 16 waves fills a CU, and a tile's evaluations are a chain
   // in every lane: tables of few tiles take smaller ones, down to 32
-  // evaluations per lane, up to one workgroup per CU, or four where a lane
-  // keeps 64 (89,285 rows of one join, K = 112: 162 -> 37 us; 9,765 rows,
-  // K = 1024: 1340 -> 43 us; with four at 32, 625,000 rows, K = 16: 39 -> 43)
+  // evaluations per lane, where that takes a seventh off the rounds of the CUs
+  // (a tile's own cost as ten evaluations; of rows with predicates, which
+  // mostly qualify seldom, a tenth count): 89,285 rows of one join, K = 112,
+  // 162 -> 37 us; 9,765 rows, K = 1024, 1340 -> 43; 625,000 rows, K = 112,
+  // 170 -> 139, but of K = 33 stay at 64 us (68 in half the tile) and, a tenth
+  // of them selected, at 27 and 34 us (31 and 40 in smaller tiles).
   P.tile = kBuildTile;
   const int parts = kBuildThreads / K;
-  for (;;) {
-    const int64_t half = P.tile / 2, per_lane = half / parts * n_joins;
-    const int64_t n_half = (n_rows + half - 1) / half;
-    if (per_lane < 32 || n_half > (per_lane < 64 ? 1 : 4) * (int64_t)ds->n_cu) break;
-    P.tile = (int32_t)half;
+  auto lane_evals = [&](int64_t tile) { return tile / parts * n_joins; };
+  auto tile_cost = [&](int64_t tile) {
+    const int64_t n = (n_rows + tile - 1) / tile;
+    return (double)((n + ds->n_cu - 1) / ds->n_cu) *
+           ((n_preds > 0 ? 0.1 : 1.0) * (double)lane_evals(tile) + 10.0);
+  };
+  for (int64_t tile = kBuildTile / 2; lane_evals(tile) >= 32; tile /= 2) {
+    if ((n_rows + tile - 1) / tile > 4ll * ds->n_cu) break;
+    if (tile_cost(tile) < 0.85 * tile_cost(P.tile)) P.tile = (int32_t)tile;
   }
   const int64_t tiles = (n_rows + P.tile - 1) / P.tile;
   const int64_t blocks = std::min<int64_t>(tiles, 4ll * ds->n_cu);
