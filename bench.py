@@ -78,12 +78,14 @@ def algorithmic_work(q, n_sel, with_preds=None):
 
 SCAN_SOURCES = ["scan_common.hpp", "build_kernels.hip", "build_params.hpp",
                 "device_math.hpp"]
+COUNT_SOURCES = ["count_kernels.hip", "count_params.hpp", "build_params.hpp",
+                 "device_math.hpp"]
 
 # Integer VALU peak of MI355X: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, one
 # 32-bit operation per lane per clock (no packed 32-bit integer issue).
 ALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
-# fp32 vector peak of MI355X (FMA = 2 flops)
-FP32_VECTOR_PEAK_TFLOPS = 157.3
+# fp32 peak of MI355X, vector and matrix units alike (FMA = 2 flops)
+FP32_PEAK_TFLOPS = 157.3
 # Algorithmic 32-bit integer operations per unit of work:
 #  hash update (key below 2^32): four Horner steps of a 61 x 32-bit
 #    multiply-add mod 2^61-1 at 6 operations (two 32 x 32 -> 64
@@ -489,13 +491,13 @@ def measure_learned(epochs=30):
             "train_samples_per_s": n * epochs / t_train,
             "feature_build_s": t_feat, "mse_first_last": [hist[0], hist[-1]],
             "qerror_heldout": res,
-            # training kernels (forward, backward, gradient sum + Adam): fp32
-            # FMA on the vector units; 2 flops per multiply-add of the three
+            # training kernels (forward and backward; gradient sum + Adam): fp32
+            # on the matrix units; 2 flops per multiply-add of the three
             # products of each layer (forward, input gradient, weight
             # gradient; the first layer has no input gradient)
             "roofline": {"bound": "alu", "achieved": train_tflops,
-                         "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
-                         "frac": train_tflops / FP32_VECTOR_PEAK_TFLOPS,
+                         "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
+                         "frac": train_tflops / FP32_PEAK_TFLOPS,
                          "traffic": None,
                          "kernel": "mlp training step (fwd, bwd, reduce+Adam)",
                          "flops_per_sample": flops_per_sample,
@@ -857,8 +859,8 @@ def run_partition_kd(args):
 
     e_part, e_merge = float(est.item()), float(est_m[0].item())
     rows = sum(tb.n_rows for tb in q.tables)
-    # dominant kernel: the fact table's binned k-D build (scan with records,
-    # counting sort by tile, one workgroup per tile); algorithmic bytes: its
+    # dominant kernel: the fact table's segmented k-D build (scan with records
+    # grouped by tile in LDS, one workgroup per tile); algorithmic bytes: its
     # three key columns and the d x 128^3 tensor written once
     t_bytes = d * w ** 3 * 4
     b = fact.n_rows * 12 + t_bytes
@@ -877,7 +879,7 @@ def run_partition_kd(args):
            "kernel_ms_per_step": kms,
            "roofline": {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS,
                         "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS, "traffic": None,
-                        "kernel": "scan2d (binned k-D build of the fact table)",
+                        "kernel": "scan2d (segmented k-D build of the fact table)",
                         "alg_bytes_per_step": b,
                         "updates_per_step": n_sel[0] * d,
                         "updates_per_s": n_sel[0] * d / s_s},
@@ -1195,7 +1197,8 @@ def run_job6a(args):
                + kernel_ms["scan_sketch"]) / 1e3
     gbs = alg_bytes / count_s / 1e9
     roofline = {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS,
-                "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS, "traffic": None,
+                "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS,
+                "traffic": measured_traffic("count_traffic_job6a.md", COUNT_SOURCES),
                 "kernel": "count", "alg_bytes_per_step": alg_bytes}
     roofline["launches_per_step"] = prof[roofline["kernel"]][0] / args.steps
     roofline["kernel_ms_per_step"] = kernel_ms[roofline["kernel"]]

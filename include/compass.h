@@ -141,8 +141,8 @@ compass_status compass_sketch_build(int64_t n_rows,
 /* compass_sketch_build_noalloc -- compass_sketch_build for callers that
  * cannot allocate memory during the call (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): same arguments,
- * same kernels, same results, but no hipMalloc, hipFree, host or pinned
- * allocation and no timing events.  Its scratch (slab of partial
+ * same results, every row hashed (nothing counted first), but no hipMalloc,
+ * hipFree, host or pinned allocation and no timing events.  Its scratch (slab of partial
  * counters, survivor buffer, seeds) is one fixed 256 MiB region of device
  * memory per GPU, held until the process ends, with the work cut to fit
  * it (fewer chunks, smaller survivor batches).  E_RANGE, before any GPU

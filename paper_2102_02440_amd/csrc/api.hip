@@ -874,6 +874,8 @@ static compass_status sketch_build_impl(
   // writing the group's counters; 3 us) and of the slab's reduction.  0.2M
   // and 1.6M rows of 15 slices of 3000 counters: 189 and 188 us at eight
   // tiles, 43 us each on average this way; 2000 rows of 7 slices: 34 and 13.
+  // (Whole calls of 1 to 48 slices of 64 to 30,000 counters and 500 to 2M
+  // rows: none slower, 44 slices of 64 counters and 20,000 rows 381 -> 26.)
   const int64_t plain_chunks = chunks;
   if (chunks * n_groups_total < n_cu && !serial) {
     const double per_ns = base.bm.pow2 ? 2.4 : 1.2;
